@@ -1794,11 +1794,10 @@ __global__ __launch_bounds__(GAL_NT) void k_gup(Ctx cx, GalArgs<T> ga)
 // anti-diagonals d = i + m j (m = 1 for the 5-point set, whose lower
 // neighbours are (i-1, j) and (i, j-1); m = 3 for the 25-point set, whose
 // lower neighbours reach (i+2, j-1) and (i-2, j)) are sets of independent
-// points, taken in order with a barrier between them.  That is n_x + m n_y
-// dependent steps per solve, so one workgroup runs the level and the leg is
-// latency-bound by construction; every per-point operation is the oracle's,
-// in its order.  Every side of a smoothing level has at least 5 cells (the
-// 25-point offsets are then in column order).
+// points, taken in order.  That is n_x + m n_y dependent steps per solve, so
+// the leg is latency-bound by construction; every per-point operation is the
+// oracle's, in its order.  Every side of a smoothing level has at least 5
+// cells (the 25-point offsets are then in column order).
 // ---------------------------------------------------------------------------
 #define HH_ILU_WG 1024
 // the pointwise phases (prolongation, residual, update) of a level with more
@@ -1806,6 +1805,8 @@ __global__ __launch_bounds__(GAL_NT) void k_gup(Ctx cx, GalArgs<T> ga)
 // workgroup: in one workgroup they would take N / 1024 dependent load
 // round trips per thread
 #define HH_ILU_PW 256
+#define HH_ILU_ROWS_WG 256            // k_ilu_up_rows: one solving and three feeding waves
+#define HH_ILU_SPIN (1 << 25)         // channel loads before a stage gives up (tens of seconds)
 #define HH_ILU_INNER_MAX (int64_t(1) << 10)
 struct IluArgs {
     LevelDev<double> fl, cl;          // level l and the coarser level l + 1
@@ -1816,6 +1817,7 @@ struct IluArgs {
                                       // 0: k_ilu_prolong, k_ilu_resid, k_ilu_update run them
     int diag;                         // 1: w in the row form's step order (IluLayout position
                                       // dd TS + t of each point); 0: w by point
+    uint64_t *chan;                   // row form: its channel (IluLayout::chan_words words)
 };
 
 // entry s (offset (s % 5 - 2, s / 5 - 2)) of row p of M_l applied to u, with
@@ -1847,51 +1849,46 @@ __device__ __forceinline__ double2 ilu_Mu(const LevelDev<double> &L, const doubl
 }
 
 // The entry sets of the triangular solves (NLO entries on each side of the
-// diagonal), the anti-diagonal step m, and the workgroup size NT of the row
-// form (k_ilu_up_rows) for the 25-point (Galerkin) and the 5-point stencils.
+// diagonal) and the anti-diagonal step m for the 25-point (Galerkin) and the
+// 5-point stencils, with the row form's shape (k_ilu_up_rows): RW rows per
+// stage, HR rows read from the stage before, chunks of S steps, XE double2
+// per ring entry.
 template <bool GAL> struct IluSet;
 template <> struct IluSet<true> {
-    static constexpr int M = 3, NLO = 12, NT = 512, RING = 9, HR = 2, HMAX = 2048, PF = 3;
+    static constexpr int M = 3, NLO = 12, RW = 32, HR = 2, S = 6, XE = 2;
     __host__ __device__ static constexpr int lo(int k) { return k; }          // s = 0 .. 11
     __host__ __device__ static constexpr int up(int k) { return 13 + k; }     // s = 13 .. 24
 };
 template <> struct IluSet<false> {
-    static constexpr int M = 1, NLO = 2, NT = 1024, RING = 2, HR = 1, HMAX = 4096, PF = 4;
+    static constexpr int M = 1, NLO = 2, RW = 64, HR = 1, S = 12, XE = 1;
     __host__ __device__ static constexpr int lo(int k) { return k == 0 ? 7 : 11; }
     __host__ __device__ static constexpr int up(int k) { return k == 0 ? 13 : 17; }
 };
 
 // Device layout of a level's ILU(0) factors, in the order the row form reads
-// them.  Where nx <= m NT all rows form one band, thread t solving rows t,
-// t + NT, ... (a row ends before the one NT below it starts); otherwise the
-// rows are split into nb bands of at most NT rows (sizes base or base + 1,
-// the first `extra` bands the larger).  Row offset r of band b is solved by
-// thread lane(r) = r mod NT, point (i, j0(b) + r) at the band's step d = i +
-// m r, and the bands' steps are numbered on from one band to the next
-// (global step dd = d0(b) + d).  The entries of one step are stored
-// lane-contiguous: entry k of lane t at (dd NLO + k) TS + t for the lower
-// set, and the diagonal (k = 0) and upper entries (k = 1 .. NLO) at (DT NLO
-// + dd (NLO + 1) + k) TS + t, where TS is the largest band rounded up to 64
-// lanes (at most NT) and DT the total step count; positions without a point,
-// and the entries of a point's neighbours outside the grid, are +0.  A wave's loads of one
-// entry are then one contiguous 1 KB block.
+// them: the rows are split into nb bands (the row form's stages) of at most RW
+// rows (sizes base or base + 1, the first `extra` bands the larger; at least
+// RW / 2 rows where nb > 1).  Row offset r of band b belongs to lane r, point
+// (i, j0(b) + r) to the band's step d = i + m r, and the bands' steps are
+// numbered on from one band to the next (global step dd = d0(b) + d).  The
+// entries of one step are stored lane-contiguous: entry k of lane t at (dd NLO
+// + k) RW + t for the lower set, and the diagonal (k = 0) and upper entries (k
+// = 1 .. NLO) at (DT NLO + dd (NLO + 1) + k) RW + t, DT the total step count;
+// positions without a point, and the entries of a point's neighbours outside
+// the grid, are +0.  A run of steps is one contiguous block, read with whole
+// cache lines in either direction.
 template <bool GAL> struct IluLayout {
     using S = IluSet<GAL>;
-    int nx, ny, nb, base, extra, TS;
+    static constexpr int TS = S::RW;
+    int nx, ny, nb, base, extra;
     int64_t DT;
     __host__ __device__ IluLayout(int nx_, int ny_) : nx(nx_), ny(ny_)
     {
-        // one band when a thread finishes a row before the row NT below it
-        // starts (nx <= m NT): thread t then owns rows t, t + NT, ...
-        nb = nx <= S::M * S::NT ? 1 : (ny + S::NT - 1) / S::NT;
+        nb = (ny + S::RW - 1) / S::RW;
         base = ny / nb;
         extra = ny % nb;
-        const int rmax = base + (extra > 0 ? 1 : 0);
-        TS = rmax > S::NT ? S::NT : (rmax + 63) / 64 * 64;
         DT = (int64_t)nb * (nx - S::M) + (int64_t)S::M * ny;
     }
-    // lane of row offset r within its band
-    __host__ __device__ static int lane(int r) { return r % S::NT; }
     __host__ __device__ int j0(int b) const { return b * base + (b < extra ? b : extra); }
     __host__ __device__ int band_of(int j) const
     {
@@ -1903,6 +1900,9 @@ template <bool GAL> struct IluLayout {
     __host__ __device__ int64_t lo(int64_t dd, int k, int t) const { return (dd * S::NLO + k) * TS + t; }
     __host__ __device__ int64_t up(int64_t dd, int k, int t) const { return (DT * S::NLO + dd * (S::NLO + 1) + k) * TS + t; }
     __host__ __device__ int64_t size() const { return DT * (2 * S::NLO + 1) * TS; }
+    // the row form's channel between stages (64-bit words): the launch number,
+    // then per solve, stage and column 4 words for each of the HR rows
+    __host__ __device__ int64_t chan_words() const { return 1 + 2 * (int64_t)nb * nx * S::HR * 4; }
 };
 
 // position of point p in w: p, or with the row form the point's layout
@@ -1915,11 +1915,11 @@ __device__ __forceinline__ int64_t ilu_wpos(const IluArgs &a, int64_t p)
     if (a.fl.g) {
         const IluLayout<true> lay(nx, ny);
         const int b = lay.band_of(j), r = j - lay.j0(b);
-        return (lay.d0(b) + i + 3 * r) * lay.TS + lay.lane(r);
+        return (lay.d0(b) + i + 3 * r) * lay.TS + r;
     }
     const IluLayout<false> lay(nx, ny);
     const int b = lay.band_of(j), r = j - lay.j0(b);
-    return (lay.d0(b) + i + r) * lay.TS + lay.lane(r);
+    return (lay.d0(b) + i + r) * lay.TS + r;
 }
 
 // the pointwise phases of the up-leg at point p: u = 0 + P e_{l+1} (bilinear,
@@ -1964,6 +1964,7 @@ __global__ __launch_bounds__(HH_ILU_PW) void k_ilu_resid(Ctx cx, IluArgs a)
     if (phase_of(cx, 0) != PH_RUN) return;
     const int64_t p = blockIdx.x * (int64_t)HH_ILU_PW + threadIdx.x;
     if (p < a.fl.N) ilu_resid_at(a, p);
+    if (p == 0 && a.diag) a.chan[0] = a.chan[0] + 1;   // the solves' launch number
 }
 __global__ __launch_bounds__(HH_ILU_PW) void k_ilu_update(Ctx cx, IluArgs a)
 {
@@ -1996,11 +1997,11 @@ __global__ __launch_bounds__(HH_ILU_WG) void k_ilu_up(Ctx cx, IluArgs a)
     auto pos = [&](int i, int j, int64_t &dd, int &t) {
         if (gal) {
             const int b = lg.band_of(j), r = j - lg.j0(b);
-            t = lg.lane(r);
+            t = r;
             dd = lg.d0(b) + i + 3 * r;
         } else {
             const int b = l5.band_of(j), r = j - l5.j0(b);
-            t = l5.lane(r);
+            t = r;
             dd = l5.d0(b) + i + r;
         }
     };
@@ -2055,201 +2056,274 @@ __global__ __launch_bounds__(HH_ILU_WG) void k_ilu_up(Ctx cx, IluArgs a)
         for (int64_t p = tid; p < N; p += HH_ILU_WG) ilu_update_at(a, p);
 }
 
-// The same up-leg with the triangular solves in the pipelined row form
-// (NT = 1024 threads for the 5-point set; 512 for the 25-point one, whose
-// 2 x 12 factors in flight need the registers of a 512-thread workgroup).
-// Thread t owns row t, and on anti-diagonal d it solves point (d - m t, t),
-// so its points come left to right (right to left in the backward solve) one
-// step after another.  A level of more rows than threads runs as one pass
-// with thread t owning rows t, t + NT, ... where a row ends before the row NT
-// below it starts (nx <= m NT), and otherwise in bands of at most NT rows.
-// The values of the last RING diagonals sit in LDS (slot d mod RING, entry
-// lane t of the thread that solved the point): the neighbours below a point
-// lie on the 8 diagonals before it (m = 3) or the one before (m = 1), in the
-// same or the two lanes before (wrapping from lane 0 to NT - 1 in the one
-// pass), and those above on as many after it, so no neighbour value is read
-// from global memory, and a slot is rewritten only after every read of its
-// previous diagonal.  Bands run one after
-// another (bottom up forward, top down backward); the rows a band reads from
-// the band before it (two with m = 3, one with m = 1) are kept in an LDS halo
-// by column, each entry rewritten by the band's own boundary rows only after
-// its last read (bands have at least 3 rows).  The factors and the
-// right-hand side of a thread's points are loaded PF steps before they are
-// needed (3 with m = 3, 4 with m = 1), behind the barriers of the steps in
-// between.  Values and operation order are k_ilu_up's.
-template <bool GAL, int NT, bool MULTI>
-__global__ __launch_bounds__(NT) void k_ilu_up_rows(Ctx cx, IluArgs a)
+// The row form of the triangular solves: the level's rows are cut into stages
+// of at most RW rows (IluLayout's bands), one workgroup per stage, all stages
+// in flight at once as a pipeline.  Within a stage, row r solves point (d - m r,
+// r) on step d; stage b + 1 follows stage b a little more than m RW steps
+// behind, reading the rows it needs (two with m = 3, one with m = 1) from a
+// channel in global memory.  The backward solve is the same walk mirrored
+// (columns right to left, rows bottom up, the last stage first): forward step
+// d of row r is backward step nd - 1 - d of row R - 1 - r, so one layout
+// serves both.
+//
+// A workgroup is one solving wave and three waves that feed it, one per SIMD:
+//   * the solving wave walks S steps (a chunk) without a barrier.  25-point
+//     set: two lanes per row, one for the real and one for the imaginary part
+//     (48 FP64 instructions per step instead of 96); 5-point set: one lane
+//     per row.  A row needs one new value per row above and step (column i + 2
+//     resp. i); the rest of its 5-column windows stay in registers.  New
+//     values pass from row to row through an LDS ring of 3 chunks of steps;
+//   * the feeding waves stream the chunk after next's factors and right-hand
+//     side into registers three chunks ahead and write them to the other of
+//     two LDS buffers; one of them also waits for the channel of the stage
+//     before and puts its values into the ring as rows -1 and -2, another
+//     publishes this stage's last rows;
+//   * one barrier per chunk.
+// Channel words carry 32 bits of data and the launch's number (epoch), stored
+// and loaded as relaxed 64-bit atomics at device scope: a word with the
+// current number is the value, so no fence and no clearing is needed.
+// Bound: the dependent steps, n_x + about 1.3 m n_y per solve, each about the
+// issue time of one wave's instructions.  One workgroup per level took 0.8-1.2
+// us per step (every row's loads, a barrier and the neighbour reads); as a
+// pipeline a 25-point step takes about 0.3 us, a 5-point one 0.16.  ILU(0)
+// V-cycle, 384^2: 3.46 -> 1.49 ms; 1280^2: 17.0 -> 5.1 ms.
+// Values and operation order are k_ilu_up's: a product f q is taken as
+// (f.x a + f.y b) with (a, b) = (q.x, -q.y) resp. (q.y, q.x), which rounds as
+// cmul does; values outside the grid are +0 and their factors +0.
+__device__ __forceinline__ double ilu_swap(double v) { return dpp_x<0xB1>(v); }   // the other lane of a row's pair
+__device__ __forceinline__ double ilu_flip(double v, int mask)
+{
+    return __hiloint2double(__double2hiint(v) ^ mask, __double2loint(v));
+}
+
+// LDS of the row form: two chunk buffers (factors, diagonal, right-hand
+// side) and the ring of solved values, rows -HR .. RW - 1 per step
+template <bool GAL> struct IluLds {
+    using S = IluSet<GAL>;
+    double2 fac[2][S::S * (S::NLO + 1) * S::RW];
+    double2 rhs[2][S::S * S::RW];
+    double2 ring[3 * S::S * (S::RW + S::HR) * S::XE];
+    int failed;
+};
+
+// One chunk of the solving wave, 25-point set.  lane = 2 row + part.
+template <bool FWD>
+__device__ __forceinline__ void ilu_chunk(IluLds<true> &sm, int c, int row, int R, int nx, int d0, double *wst,
+                                          double2 (&W1)[6], double2 (&W2)[6], double2 (&O)[2])
+{
+    using S = IluSet<true>;
+    constexpr int NF = FWD ? S::NLO : S::NLO + 1, ST = (S::RW + S::HR) * S::XE;
+    const int part = threadIdx.x & 1;
+    const int mneg = part == 0 ? (int)0x80000000 : 0, mdiv = part == 0 ? 0 : (int)0x80000000;
+    const double2 *fac = sm.fac[c & 1] + (FWD ? row : (row < R ? R - 1 - row : 0));
+    const double *rhs = (const double *)(sm.rhs[c & 1] + (FWD ? row : (row < R ? R - 1 - row : 0))) + part;
+    // ring entry of this row: rows -2, -1 lead; an entry is (x, -y, y, x)
+    double2 *cur = sm.ring + (c % 3) * S::S * ST + row * S::XE + part;
+    const double2 *prev = sm.ring + ((c + 2) % 3) * S::S * ST + row * S::XE + part;
+    const int i0 = (c - 1) * S::S - S::M * row;
+#pragma unroll
+    for (int s = 0; s < S::S; ++s) {
+        const int i = i0 + s, ss = FWD ? s : S::S - 1 - s;
+        const bool act = (unsigned)i < (unsigned)nx && row < R;
+        W1[s] = (s >= 1 ? cur + (s - 1) * ST : prev + (S::S - 1) * ST)[1 * S::XE];
+        W2[s] = (s >= 4 ? cur + (s - 4) * ST : prev + (S::S + s - 4) * ST)[0];
+        double v = rhs[ss * S::RW * 2];
+        auto term = [&](int k, double2 q) {
+            const double2 f = fac[(ss * NF + (FWD ? k : 1 + k)) * S::RW];
+            v = v - (f.x * q.x + f.y * q.y);
+        };
+        const double2 o1 = O[(s + 1) & 1], o2 = O[s & 1];
+        if (FWD) {
+#pragma unroll
+            for (int k = 0; k < 5; ++k) term(k, W2[(s + 2 + k) % 6]);
+#pragma unroll
+            for (int k = 0; k < 5; ++k) term(5 + k, W1[(s + 2 + k) % 6]);
+            term(10, o2);
+            term(11, o1);
+        } else {
+            term(0, o1);
+            term(1, o2);
+#pragma unroll
+            for (int k = 0; k < 5; ++k) term(2 + k, W1[(s + 6 - k) % 6]);
+#pragma unroll
+            for (int k = 0; k < 5; ++k) term(7 + k, W2[(s + 6 - k) % 6]);
+            const double2 dg = fac[ss * NF * S::RW];
+            const double num = v * dg.x + ilu_flip(ilu_swap(v), mdiv) * dg.y;
+            v = num / (dg.x * dg.x + dg.y * dg.y);
+        }
+        v = act ? v : 0.0;
+        const double2 e = cmk<double>(v, ilu_flip(ilu_swap(v), mneg));
+        O[s & 1] = e;
+        (cur + s * ST)[S::HR * S::XE] = e;
+        if (act) ((HH_GLOBAL double *)wst)[(int64_t)(FWD ? d0 + (c - 1) * S::S + s : d0 - ((c - 1) * S::S + s)) * S::RW * 2] = v;
+    }
+}
+
+// One chunk of the solving wave, 5-point set.  lane = row.
+template <bool FWD>
+__device__ __forceinline__ void ilu_chunk(IluLds<false> &sm, int c, int row, int R, int nx, int d0, double *wst,
+                                          double2 &O)
+{
+    using S = IluSet<false>;
+    constexpr int NF = FWD ? S::NLO : S::NLO + 1, ST = (S::RW + S::HR) * S::XE;
+    const int rr = FWD ? row : (row < R ? R - 1 - row : 0);
+    const double2 *fac = sm.fac[c & 1] + rr, *rhs = sm.rhs[c & 1] + rr;
+    double2 *cur = sm.ring + (c % 3) * S::S * ST + row;
+    const double2 *prev = sm.ring + ((c + 2) % 3) * S::S * ST + row;
+    const int i0 = (c - 1) * S::S - row;
+#pragma unroll
+    for (int s = 0; s < S::S; ++s) {
+        const int i = i0 + s, ss = FWD ? s : S::S - 1 - s;
+        const bool act = (unsigned)i < (unsigned)nx && row < R;
+        const double2 q = (s >= 1 ? cur + (s - 1) * ST : prev + (S::S - 1) * ST)[0];
+        double2 v = rhs[ss * S::RW];
+        const double2 *f = fac + ss * NF * S::RW;
+        if (FWD) {
+            v = csub<double>(v, cmul<double>(f[0], q));
+            v = csub<double>(v, cmul<double>(f[S::RW], O));
+        } else {
+            v = csub<double>(v, cmul<double>(f[S::RW], O));
+            v = csub<double>(v, cmul<double>(f[2 * S::RW], q));
+            v = cdiv<double>(v, f[0]);
+        }
+        v.x = act ? v.x : 0.0;
+        v.y = act ? v.y : 0.0;
+        O = v;
+        (cur + s * ST)[S::HR] = v;
+        if (act) stg((double2 *)wst, (int64_t)(FWD ? d0 + (c - 1) * S::S + s : d0 - ((c - 1) * S::S + s)) * S::RW, v);
+    }
+}
+
+// Stage b of one solve.
+template <bool GAL, bool FWD>
+__device__ __forceinline__ void ilu_stage(IluLds<GAL> &sm, const IluArgs &a, const IluLayout<GAL> &lay, int b, uint32_t epoch)
 {
     using S = IluSet<GAL>;
-    // NT below the layout's S::NT serves levels of at most NT rows (one band,
-    // whose layout does not depend on the workgroup size); MULTI (one band of
-    // more rows than threads) needs the layout's NT
-    static_assert(NT <= S::NT && NT % 64 == 0 && (!MULTI || NT == S::NT), "the factor layout's workgroup size");
-    constexpr int M = S::M, NK = S::NLO, RG = S::RING, HR = S::HR, HM = S::HMAX;
-    // the ring of the last RG diagonals (slot d mod RG, entry t), then the
-    // halo, then one entry holding +0 (the value of a neighbour outside the
-    // grid)
-    __shared__ double2 lds[RG * NT + HR * HM + 1];
-    constexpr int HB = RG * NT, Z0 = RG * NT + HR * HM;
-    if (phase_of(cx, 0) != PH_RUN) return;
-    const LevelDev<double> L = a.fl;
-    const int nx = L.n[0], ny = L.n[1];
-    const int64_t N = L.N;
-    const double2 *__restrict__ F = L.ilu;
-    double2 *w = L.w;
-    const double2 zero = cmk<double>(0.0, 0.0);
-    const int t = threadIdx.x;
-    if (t == 0) lds[Z0] = zero;
-    if (a.inner) {
-        for (int64_t p = t; p < N; p += NT) ilu_prolong_at(a, p);
+    constexpr int NF = FWD ? S::NLO : S::NLO + 1;           // factor entries per point and step
+    constexpr int NL = 3 * 64, LF = S::S * NF * S::RW / NL, LW = S::S * S::RW / NL;   // loads per feeding thread
+    static_assert(S::S * NF * S::RW % NL == 0 && S::S * S::RW % NL == 0, "a chunk is whole loads of the feeding waves");
+    constexpr int ST = (S::RW + S::HR) * S::XE;
+    const int nx = lay.nx, R = lay.j0(b + 1) - lay.j0(b), nd = nx + S::M * (R - 1);
+    const int64_t D0 = lay.d0(b);
+    // chunk c covers steps (c - 1) S .. c S - 1: chunk 0 only fills the
+    // windows with the rows above; a multiple of the feeding waves' 3 buffers
+    const int nch = (1 + (nd + S::S - 1) / S::S + 2) / 3 * 3;
+    const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6), lane = threadIdx.x & 63;
+    for (int t = threadIdx.x; t < 3 * S::S * ST; t += HH_ILU_ROWS_WG) sm.ring[t] = cmk<double>(0.0, 0.0);
+    __syncthreads();
+    if (wave == 0) {
+        const int row = GAL ? lane >> 1 : lane;
+        // this lane's place in w at step 0 (backward: of forward step nd - 1)
+        const int rr = FWD ? row : (row < R ? R - 1 - row : 0);
+        double *wst = (double *)(a.fl.w + D0 * S::RW + rr) + (GAL ? (lane & 1) : 0);
+        const int d0 = FWD ? 0 : nd - 1;
+        const double2 zero = cmk<double>(0.0, 0.0);
+        double2 W1[6] = {zero, zero, zero, zero, zero, zero}, W2[6] = {zero, zero, zero, zero, zero, zero}, O[2] = {zero, zero};
+        for (int c = 0; c < nch; ++c) {
+            __syncthreads();
+            if constexpr (GAL) ilu_chunk<FWD>(sm, c, row, R, nx, d0, wst, W1, W2, O);
+            else ilu_chunk<FWD>(sm, c, row, R, nx, d0, wst, O[0]);
+        }
         __syncthreads();
-        for (int64_t p = t; p < N; p += NT) ilu_resid_at(a, p);
+    } else {
+        const int ft = (int)threadIdx.x - 64;
+        const double2 *F = a.fl.ilu + (FWD ? lay.lo(D0, 0, 0) : lay.up(D0, 0, 0));
+        const double2 *W = a.fl.w + D0 * S::RW;
+        double2 q[3][LF + LW];
+        // the loads of chunk c (its steps are consecutive in memory; indexes
+        // outside the stage are clamped, their steps solve no point)
+        auto fetch = [&](int c, double2(&v)[LF + LW]) {
+            const int d = max(min(FWD ? (c - 1) * S::S : nd - c * S::S, nd - 1), 1 - S::S);   // first step in memory order
+            const int lo = max(-d, 0), hi = min(nd - d, S::S);
+            const double2 *Fd = F + (int64_t)d * (NF * S::RW), *Wd = W + (int64_t)d * S::RW;
+#pragma unroll
+            for (int m = 0; m < LF; ++m) v[m] = ldg(Fd, min(max(ft + m * NL, lo * NF * S::RW), hi * NF * S::RW - 1));
+#pragma unroll
+            for (int m = 0; m < LW; ++m) v[LF + m] = ldg(Wd, min(max(ft + m * NL, lo * S::RW), hi * S::RW - 1));
+        };
+        // channel items of a chunk, one per lane: step, halo row h (row -1 - h
+        // of the reader, row R - 1 - h of the writer), part, 32-bit half
+        constexpr int NI = S::S * S::HR * 4;
+        static_assert(NI <= 64, "one channel item per lane");
+        const int half = lane & 1, part = lane >> 1 & 1, h = S::HR == 2 ? lane >> 2 & 1 : 0, is = lane / (4 * S::HR);
+        const int64_t cw = (int64_t)nx * S::HR * 4;      // words per stage
+        uint64_t *ch = a.chan + 1 + (FWD ? 0 : lay.nb * cw) + (h * 4 + part * 2 + half);
+        const bool first = FWD ? b == 0 : b == lay.nb - 1;
+        auto poll = [&](int c) {
+            const int col = (c - 1) * S::S + is + S::M * (1 + h);
+            const bool need = !first && lane < NI && col >= 0 && col < nx;
+            const uint64_t *p = ch + (FWD ? b - 1 : b + 1) * cw + (int64_t)(need ? col : 0) * (S::HR * 4);
+            uint64_t v = 0;
+            bool ok = !need;
+            for (int n = 0;; ++n) {
+                if (!ok) {
+                    v = __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                    ok = (int)((uint32_t)(v >> 32) - epoch) >= 0;
+                }
+                if (!__any(!ok)) break;
+                // a stage before that never comes (it cannot, with every
+                // workgroup resident) ends as NaN instead of a hang
+                if (n >= (sm.failed ? 0 : HH_ILU_SPIN)) {
+                    sm.failed = 1;
+                    break;
+                }
+            }
+            uint32_t w = (uint32_t)v;
+            if (need && !ok) w = half ? 0x7ff80000u : 0u;
+            if (lane < NI) {
+                uint32_t *x = (uint32_t *)(sm.ring + ((c % 3) * S::S + is) * ST + (S::HR - 1 - h) * S::XE) + half;
+                if constexpr (GAL) {
+                    x[part ? 4 : 0] = w;
+                    x[part ? 2 : 6] = part && half ? w ^ 0x80000000u : w;
+                } else {
+                    x[part ? 2 : 0] = w;
+                }
+            }
+        };
+        auto publish = [&](int c) {
+            const int row = R - 1 - h, col = (c - 1) * S::S + is - S::M * row;
+            if (lane < NI && col >= 0 && col < nx) {
+                const uint32_t *x = (const uint32_t *)(sm.ring + ((c % 3) * S::S + is) * ST + (row + S::HR) * S::XE) + half;
+                const uint64_t v = (uint64_t)epoch << 32 | x[part ? (GAL ? 4 : 2) : 0];
+                __hip_atomic_store(ch + b * cw + (int64_t)col * (S::HR * 4), v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            }
+        };
+#pragma unroll
+        for (int u = 0; u < 3; ++u) fetch(1 + u, q[u]);
+        if (wave == 1) poll(0);
+        for (int c0 = 0; c0 < nch; c0 += 3) {
+#pragma unroll
+            for (int u = 0; u < 3; ++u) {
+                const int c = c0 + u;
+                __syncthreads();
+                double2 *f = sm.fac[(c + 1) & 1] + ft, *w = sm.rhs[(c + 1) & 1] + ft;
+#pragma unroll
+                for (int m = 0; m < LF; ++m) f[m * NL] = q[u][m];
+#pragma unroll
+                for (int m = 0; m < LW; ++m) w[m * NL] = q[u][LF + m];
+                fetch(c + 4, q[u]);
+                if (wave == 1) poll(c + 1);
+                if (wave == 2 && c > 0) publish(c - 1);
+            }
+        }
+        __syncthreads();
+        if (wave == 2) publish(nch - 1);
     }
     __syncthreads();
-    // nb bands of ny / nb or ny / nb + 1 rows (the layout's); the halo is used
-    // (and nx <= HM holds) only when nb > 1
-    const IluLayout<GAL> lay(nx, ny);
-    const int nb = lay.nb;
-    const bool banded = nb > 1;
-    auto band0 = [&](int bi) { return lay.j0(bi); };
-    auto slot = [&](int d, int tt) -> int { return (d % RG) * NT + tt; };
-    // the factors and the right-hand side (and, backward, the diagonal) of
-    // a thread's points are prefetched PF steps ahead into PF buffers with
-    // fixed roles: step d uses buffer d mod PF, and refills it with the point
-    // the thread solves at step d + PF.  Every thread loads on every step, a
-    // thread without a point there (before its row's first point, after its
-    // last, or beyond the band) from point 0 and layout position 0, so the
-    // same number of loads follows each refill on every path and the wait
-    // before a use is for that buffer's loads only, while idle lanes add one
-    // cache line per load; the active lanes of a wave read lane-contiguous
-    // factors (IluLayout); a factor of a neighbour outside the grid is loaded
-    // but never used.  The loops start PF steps early (loads only), so no
-    // buffer needs filling before them.
-    constexpr int PF = S::PF, G = GAL ? 4 : 2;   // G divides NK
-    double2 fq[PF][NK], rq[PF], dq[PF];
-    auto fetch = [&](bool act, int64_t dd, bool lower, double2(&fv)[NK], double2 &rv, double2 &dv) {
-        const int64_t dc = act ? dd : 0;
-        const int tc = act ? t : 0;
-        rv = ldg(w, dc * lay.TS + tc);
-        if (lower) {
-#pragma unroll
-            for (int k = 0; k < NK; ++k) fv[k] = ldg(F, lay.lo(dc, k, tc));
-        } else {
-            dv = ldg(F, lay.up(dc, 0, tc));
-#pragma unroll
-            for (int k = 0; k < NK; ++k) fv[k] = ldg(F, lay.up(dc, 1 + k, tc));
-        }
-    };
-    // forward: y = r - sum over the neighbours below, columns ascending
-    for (int bi = 0; bi < nb; ++bi) {
-        const int j0 = band0(bi), R = band0(bi + 1) - j0;
-        const int nd = (nx - 1) + M * (R - 1) + 1;
-        const int64_t D0 = lay.d0(bi);
-        // the row offset r and column i the thread solves at step d: row t,
-        // or with more rows than threads (MULTI: one band, nx <= M NT) the
-        // row t + k NT whose steps contain d
-        auto locate = [&](int d, int &r, int &i) -> bool {
-            const int q = d - M * t;
-            const int k = MULTI && q >= 0 ? q / (M * NT) : 0;
-            r = t + k * NT;
-            i = q - k * (M * NT);
-            return r < R && i >= 0 && i < nx;
-        };
-        auto fwd = [&](int d, double2(&fv)[NK], double2 &rv, double2 &dv) {
-            int r, i;
-            if (locate(d, r, i)) {
-                const int j = j0 + r;
-                // the neighbour values are read G at a time, then their terms
-                // are taken in order; for a neighbour outside the grid both
-                // factors are +0 (the layout stores its entry as +0, and it
-                // reads the +0 entry of LDS), and subtracting their product
-                // (+0, +0) leaves y as it is
-                double2 y = rv;
-#pragma unroll
-                for (int g = 0; g < NK; g += G) {
-                    double2 q[G];
-                    bool in[G];
-                    int ix[G];
-#pragma unroll
-                    for (int k = g; k < g + G; ++k) {
-                        const int sk = S::lo(k), dx = sk % 5 - 2, dy = sk / 5 - 2;
-                        in[k - g] = i + dx >= 0 && i + dx < nx && j + dy >= 0;
-                        const int ir = ((d + dx + M * dy + RG) % RG) * NT + (MULTI ? (t + dy + NT) % NT : t + dy);
-                        const int ih = HB + (HR + r + dy) * HM + i + dx;
-                        ix[k - g] = in[k - g] ? (dy >= 0 || r + dy >= 0 ? ir : ih) : Z0;
-                    }
-#pragma unroll
-                    for (int k = 0; k < G; ++k) q[k] = lds[ix[k]];
-#pragma unroll
-                    for (int k = g; k < g + G; ++k) y = csub<double>(y, cmul<double>(fv[k], q[k - g]));
-                }
-                lds[slot(d, t)] = y;
-                if (banded && r >= R - HR) lds[HB + (r - (R - HR)) * HM + i] = y;
-                stg(w, (D0 + d) * lay.TS + t, y);
-            }
-            int rn, in_;
-            const bool an = locate(d + PF, rn, in_);
-            fetch(an, D0 + d + PF, true, fv, rv, dv);
-            __syncthreads();
-        };
-        for (int d0 = -PF; d0 < nd; d0 += PF) {
-#pragma unroll
-            for (int b = 0; b < PF; ++b) fwd(d0 + b, fq[b], rq[b], dq[b]);
-        }
-    }
-    // backward: z = (y - sum over the neighbours above, columns ascending) / u_12
-    for (int bi = nb - 1; bi >= 0; --bi) {
-        const int j0 = band0(bi), R = band0(bi + 1) - j0;
-        const int nd = (nx - 1) + M * (R - 1) + 1;
-        const int64_t D0 = lay.d0(bi);
-        auto locate = [&](int d, int &r, int &i) -> bool {
-            const int q = d - M * t;
-            const int k = MULTI && q >= 0 ? q / (M * NT) : 0;
-            r = t + k * NT;
-            i = q - k * (M * NT);
-            return r < R && i >= 0 && i < nx;
-        };
-        auto bwd = [&](int d, double2(&fv)[NK], double2 &rv, double2 &dv) {
-            int r, i;
-            if (locate(d, r, i)) {
-                const int j = j0 + r;
-                double2 z = rv;
-#pragma unroll
-                for (int g = 0; g < NK; g += G) {
-                    double2 q[G];
-                    bool in[G];
-                    int ix[G];
-#pragma unroll
-                    for (int k = g; k < g + G; ++k) {
-                        const int sk = S::up(k), dx = sk % 5 - 2, dy = sk / 5 - 2;
-                        in[k - g] = i + dx >= 0 && i + dx < nx && j + dy < ny;
-                        const int ir = ((d + dx + M * dy) % RG) * NT + (MULTI ? (t + dy) % NT : t + dy);
-                        const int ih = HB + (r + dy - R) * HM + i + dx;
-                        ix[k - g] = in[k - g] ? (dy <= 0 || r + dy < R ? ir : ih) : Z0;
-                    }
-#pragma unroll
-                    for (int k = 0; k < G; ++k) q[k] = lds[ix[k]];
-#pragma unroll
-                    for (int k = g; k < g + G; ++k) z = csub<double>(z, cmul<double>(fv[k], q[k - g]));
-                }
-                z = cdiv<double>(z, dv);
-                lds[slot(d, t)] = z;
-                if (banded && r < HR) lds[HB + r * HM + i] = z;
-                stg(w, (D0 + d) * lay.TS + t, z);
-            }
-            int rn, in_;
-            const bool an = locate(d - PF, rn, in_);
-            fetch(an, D0 + d - PF, false, fv, rv, dv);
-            __syncthreads();
-        };
-        // the first block (from nd rounded up to a multiple of PF) only loads
-        for (int d0 = (nd + PF - 1) / PF * PF; d0 >= 0; d0 -= PF) {
-#pragma unroll
-            for (int b = PF - 1; b >= 0; --b) bwd(d0 + b, fq[b], rq[b], dq[b]);
-        }
-    }
-    if (a.inner)
-        for (int64_t p = t; p < N; p += NT) ilu_update_at(a, p);
+}
+
+template <bool GAL>
+__global__ __launch_bounds__(HH_ILU_ROWS_WG, 1) void k_ilu_up_rows(Ctx cx, IluArgs a)
+{
+    __shared__ IluLds<GAL> sm;
+    if (phase_of(cx, 0) != PH_RUN) return;
+    const IluLayout<GAL> lay(a.fl.n[0], a.fl.n[1]);
+    const uint32_t epoch = (uint32_t)a.chan[0];
+    if (threadIdx.x == 0) sm.failed = 0;
+    const int g = (int)blockIdx.x, G = (int)gridDim.x;
+    int b = g;
+    for (; b < lay.nb; b += G) ilu_stage<GAL, true>(sm, a, lay, b, epoch);
+    for (b -= G; b >= 0; b -= G) ilu_stage<GAL, false>(sm, a, lay, b, epoch);
 }
 
 // ---------------------------------------------------------------------------

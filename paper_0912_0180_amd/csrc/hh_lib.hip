@@ -114,10 +114,9 @@ template <typename T> static TailTab tail_table(const LevelDev<T> *Lh, const Hos
 // (IluLayout: by band, step and entry, lane-contiguous), from the host's 25
 // planes of N points; the level's stencil is the Galerkin one (the 25-point
 // sets) when it has Galerkin entries
-static size_t ilu_device_count(const HostLevel &L)
+static size_t ilu_device_count(int nx, int ny, bool gal)
 {
-    return L.gal.empty() ? (size_t)IluLayout<false>(L.n[0], L.n[1]).size()
-                         : (size_t)IluLayout<true>(L.n[0], L.n[1]).size();
+    return gal ? (size_t)IluLayout<true>(nx, ny).size() : (size_t)IluLayout<false>(nx, ny).size();
 }
 template <bool GAL> static void ilu_pack_set(const HostLevel &L, std::vector<double2> &out)
 {
@@ -129,7 +128,7 @@ template <bool GAL> static void ilu_pack_set(const HostLevel &L, std::vector<dou
         const int j0 = lay.j0(b), R = lay.j0(b + 1) - j0;
         for (int r = 0; r < R; ++r)
             for (int i = 0; i < nx; ++i) {
-                const int j = j0 + r, t = lay.lane(r);
+                const int j = j0 + r, t = r;
                 const int64_t p = i + (int64_t)nx * j, dd = lay.d0(b) + i + S::M * r;
                 // the entry of a neighbour outside the grid is +0 exactly: the
                 // kernels multiply it by a +0 neighbour value
@@ -143,16 +142,21 @@ template <bool GAL> static void ilu_pack_set(const HostLevel &L, std::vector<dou
             }
     }
 }
-// the up-leg's work array: by point, or in the row form's step order
-static size_t ilu_w_count(const HostLevel &L)
+// the up-leg's work array: by point, or in the row form's step order; the row
+// form's channel follows it
+static size_t ilu_w_values(int nx, int ny, bool gal)
 {
-    const size_t d = L.gal.empty() ? (size_t)(IluLayout<false>(L.n[0], L.n[1]).DT * IluLayout<false>(L.n[0], L.n[1]).TS)
-                                   : (size_t)(IluLayout<true>(L.n[0], L.n[1]).DT * IluLayout<true>(L.n[0], L.n[1]).TS);
-    return std::max((size_t)L.N, d);
+    const int64_t d = gal ? IluLayout<true>(nx, ny).DT * IluLayout<true>::TS : IluLayout<false>(nx, ny).DT * IluLayout<false>::TS;
+    return (size_t)std::max((int64_t)nx * ny, d);
 }
+static size_t ilu_chan_words(int nx, int ny, bool gal)
+{
+    return (size_t)(gal ? IluLayout<true>(nx, ny).chan_words() : IluLayout<false>(nx, ny).chan_words());
+}
+static size_t ilu_w_count(int nx, int ny, bool gal) { return ilu_w_values(nx, ny, gal) + (ilu_chan_words(nx, ny, gal) + 1) / 2; }
 static std::vector<double2> ilu_device_pack(const HostLevel &L)
 {
-    std::vector<double2> out(ilu_device_count(L), double2{0.0, 0.0});
+    std::vector<double2> out(ilu_device_count(L.n[0], L.n[1], !L.gal.empty()), double2{0.0, 0.0});
     if (L.gal.empty()) ilu_pack_set<false>(L, out);
     else ilu_pack_set<true>(L, out);
     return out;
@@ -213,8 +217,8 @@ hh_status grid_upload(hh_grid *g)
             F.ilu = nullptr;
             F.w = nullptr;
             if (!L.ilu.empty()) {
-                D.ilu = c.take<double2>(ilu_device_count(L));
-                D.w = c.take<double2>(ilu_w_count(L));
+                D.ilu = c.take<double2>(ilu_device_count(L.n[0], L.n[1], !L.gal.empty()));
+                D.w = c.take<double2>(ilu_w_count(L.n[0], L.n[1], !L.gal.empty()));
             } else {
                 D.ilu = nullptr;
                 D.w = nullptr;
@@ -271,6 +275,9 @@ hh_status grid_upload(hh_grid *g)
         if (!L.ilu.empty()) {
             const std::vector<double2> pk = ilu_device_pack(L);
             HIPCHK(put64(g->L64h[l].ilu, pk.data(), sizeof(double2) * pk.size()));
+            // the channel starts at launch number 0
+            const std::vector<uint64_t> ch(ilu_chan_words(L.n[0], L.n[1], !L.gal.empty()), 0);
+            HIPCHK(put64(g->L64h[l].w + ilu_w_values(L.n[0], L.n[1], !L.gal.empty()), ch.data(), sizeof(uint64_t) * ch.size()));
         }
         std::vector<float> p32(L.N);
         for (int64_t i = 0; i < L.N; ++i) p32[i] = (float)L.phi[i];
@@ -1118,6 +1125,17 @@ template <typename T> static TailArgs<T> tail_args(const Plan &pl)
     return a;
 }
 
+// Workgroups of the row form: a stage runs for about nx + m RW steps and the
+// next one starts m RW steps or more behind it, so at most 2 + nx / (m RW) are
+// ever in flight; a workgroup takes stages g, g + G, ... in order.  All of them
+// must be resident at once (they wait for each other): at most 32, one per CU
+// (LDS), leaves room for as many launches as the device has queues.
+template <bool GAL> static int ilu_groups(int nx, int ny)
+{
+    using S = IluSet<GAL>;
+    return std::min(std::min(IluLayout<GAL>(nx, ny).nb, 2 + nx / (S::M * S::RW)), 32);
+}
+
 template <int DIM, typename T>
 static void vcycle_t(const Plan &pl, int fsel, int osel, const void *fptr, void *optr, hipStream_t s)
 {
@@ -1171,45 +1189,24 @@ static void vcycle_t(const Plan &pl, int fsel, int osel, const void *fptr, void 
                 a.f = l == 0 ? (const double2 *)fptr : lh.d[l].f;
                 a.u = l == 0 ? (double2 *)optr : lh.d[l].e;
                 a.omega = pl.omega1;
-                // the pipelined row form with the recent diagonals in LDS,
-                // in bands where a level has more rows than the workgroup
-                // threads (then its rows must fit the LDS halo), and w in its
-                // step order; HH_ILU_GLOBAL: the global-memory form on every
-                // level
-                const bool rows = !getenv("HH_ILU_GLOBAL");
+                // the row form with w in its step order and the pointwise
+                // phases grid-wide; HH_ILU_GLOBAL: the global-memory form on
+                // every level, its pointwise phases grid-wide above
+                // HH_ILU_INNER_MAX points (HH_ILU_FUSED: never)
+                const bool rows = !getenv("HH_ILU_GLOBAL"), gal = a.fl.g != nullptr;
                 const int nx = a.fl.n[0], ny = a.fl.n[1];
-                const int form = !rows ? 0
-                                 : a.fl.g ? (ny <= IluSet<true>::NT || nx <= IluSet<true>::HMAX ? 1 : 0)
-                                          : (ny <= IluSet<false>::NT || nx <= IluSet<false>::HMAX ? 2 : 0);
-                a.diag = form != 0;
-                // levels of few rows take a workgroup of as few waves (the same
-                // layout: one band either way)
-                const int wg = form == 1 ? (ny <= 64 ? 64 : ny <= 128 ? 128 : IluSet<true>::NT)
-                                         : form == 2 ? IluSet<false>::NT : HH_ILU_WG;
-                // the pointwise phases run grid-wide except on levels of at
-                // most HH_ILU_INNER_MAX points in a full-size workgroup
-                // (HH_ILU_FUSED: inside the solve kernel always)
-                a.inner = ((a.fl.N <= HH_ILU_INNER_MAX && wg >= 512) || getenv("HH_ILU_FUSED")) ? 1 : 0;
+                a.diag = rows ? 1 : 0;
+                a.chan = (uint64_t *)(a.fl.w + ilu_w_values(nx, ny, gal));
+                a.inner = !rows && (a.fl.N <= HH_ILU_INNER_MAX || getenv("HH_ILU_FUSED")) ? 1 : 0;
                 const dim3 pg((unsigned)((a.fl.N + HH_ILU_PW - 1) / HH_ILU_PW));
                 if (!a.inner) {
                     hipLaunchKernelGGL(k_ilu_prolong, pg, dim3(HH_ILU_PW), 0, s, c, a);
                     hipLaunchKernelGGL(k_ilu_resid, pg, dim3(HH_ILU_PW), 0, s, c, a);
                 }
-                // one band of more rows than threads: the multi-row instance
-                const bool multi = form == 1 ? IluLayout<true>(nx, ny).nb == 1 && ny > IluSet<true>::NT
-                                             : form == 2 && IluLayout<false>(nx, ny).nb == 1 && ny > IluSet<false>::NT;
-                if (form == 1 && wg == 64)
-                    hipLaunchKernelGGL((k_ilu_up_rows<true, 64, false>), dim3(1), dim3(64), 0, s, c, a);
-                else if (form == 1 && wg == 128)
-                    hipLaunchKernelGGL((k_ilu_up_rows<true, 128, false>), dim3(1), dim3(128), 0, s, c, a);
-                else if (form == 1 && multi)
-                    hipLaunchKernelGGL((k_ilu_up_rows<true, IluSet<true>::NT, true>), dim3(1), dim3(IluSet<true>::NT), 0, s, c, a);
-                else if (form == 1)
-                    hipLaunchKernelGGL((k_ilu_up_rows<true, IluSet<true>::NT, false>), dim3(1), dim3(IluSet<true>::NT), 0, s, c, a);
-                else if (form == 2 && multi)
-                    hipLaunchKernelGGL((k_ilu_up_rows<false, IluSet<false>::NT, true>), dim3(1), dim3(IluSet<false>::NT), 0, s, c, a);
-                else if (form == 2)
-                    hipLaunchKernelGGL((k_ilu_up_rows<false, IluSet<false>::NT, false>), dim3(1), dim3(IluSet<false>::NT), 0, s, c, a);
+                if (rows && gal)
+                    hipLaunchKernelGGL(k_ilu_up_rows<true>, dim3(ilu_groups<true>(nx, ny)), dim3(HH_ILU_ROWS_WG), 0, s, c, a);
+                else if (rows)
+                    hipLaunchKernelGGL(k_ilu_up_rows<false>, dim3(ilu_groups<false>(nx, ny)), dim3(HH_ILU_ROWS_WG), 0, s, c, a);
                 else
                     hipLaunchKernelGGL(k_ilu_up, dim3(1), dim3(HH_ILU_WG), 0, s, c, a);
                 if (!a.inner) hipLaunchKernelGGL(k_ilu_update, pg, dim3(HH_ILU_PW), 0, s, c, a);
@@ -1373,7 +1370,8 @@ hh_status footprint_bytes(const hh_grid_desc *d, const hh_solve_opts *o, uint64_
         if (l >= 1 && d->coarse_op == HH_COARSE_GALERKIN)
             g += align256(sizeof(double2) * 25 * L[l].N) + align256(sizeof(float2) * 25 * L[l].N);
         if (l + 1 < nl && d->smoother == HH_SMOOTH_ILU0)
-            g += align256(sizeof(double2) * 25 * L[l].N) + align256(sizeof(double2) * L[l].N);
+            g += align256(sizeof(double2) * ilu_device_count(L[l].n[0], L[l].n[1], l >= 1 && d->coarse_op == HH_COARSE_GALERKIN)) +
+                 align256(sizeof(double2) * ilu_w_count(L[l].n[0], L[l].n[1], l >= 1 && d->coarse_op == HH_COARSE_GALERKIN));
     }
     g += align256(sizeof(double2) * (size_t)nc * nc) + align256(sizeof(float2) * (size_t)nc * nc);
     g += align256(TailCap<double>::BYTES) + align256(TailCap<float>::BYTES);

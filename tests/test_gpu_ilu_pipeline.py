@@ -1,0 +1,57 @@
+"""The ILU(0) row form's pipeline at the edges of its stages (32 rows with the
+25-point set, 64 with the 5-point one): one stage, a full one, one row more,
+several of unequal size, more stages than workgroups, and rows of the fewest
+columns.  The cycle equals the CPU oracle's value for value, also when it is
+repeated (each launch numbers its channel anew) and replayed from a graph."""
+import numpy as np
+import pytest
+
+from paper_0912_0180_amd import workloads as W
+
+pytestmark = pytest.mark.gpu
+
+
+def problem(nx, ny, levels, coarse_op):
+    h = 1.0 / 64
+    hi = (-0.1 + nx * h, -0.1 + ny * h)
+    d = W.base_desc(2, (nx, ny), (-0.1, -0.1), hi, (0.0, 0.0), (hi[0] - 0.1, hi[1] - 0.1), levels=levels, nu1=0,
+                    omega=0.9, coarse_op=coarse_op, smoother=1)
+    rng = np.random.default_rng(nx + 1000 * ny)
+    return d, 36.0 * (1 + 0.3 * rng.uniform(size=nx * ny)), rng
+
+
+@pytest.mark.parametrize("coarse_op", [0, 1])
+@pytest.mark.parametrize("nx,ny,levels", [(20, 60, 3), (20, 64, 3), (24, 68, 3), (20, 128, 3), (28, 132, 3), (260, 20, 3),
+                                          (20, 772, 3), (10, 400, 2), (132, 132, 3)])
+def test_stage_edges_match_oracle(oracle_mod, nx, ny, levels, coarse_op):
+    import torch
+    from paper_0912_0180_amd import hh
+    print("case", nx, ny, levels, coarse_op, flush=True)
+    d, phi, rng = problem(nx, ny, levels, coarse_op)
+    g, o = hh.Grid(d, phi), oracle_mod.Grid(d, phi)
+    for k in range(3):
+        f = rng.standard_normal(g.N) + 1j * rng.standard_normal(g.N)
+        u = g.vcycle(torch.from_numpy(f).cuda(), "c128").cpu().numpy()
+        assert np.array_equal(u, o.vcycle(f)), k
+
+
+def test_replayed_from_a_graph():
+    import torch
+    from paper_0912_0180_amd import hh
+    d, phi, rng = problem(132, 200, 3, 1)
+    g = hh.Grid(d, phi)
+    f = torch.zeros(g.N, dtype=torch.complex128, device="cuda")
+    u = torch.empty_like(f)
+    s = torch.cuda.Stream()
+    with torch.cuda.stream(s):
+        g.vcycle(f, "c128", out=u)
+    s.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=s):
+        g.vcycle(f, "c128", out=u)
+    for k in range(4):
+        f.copy_(torch.from_numpy(rng.standard_normal(g.N) + 1j * rng.standard_normal(g.N)))
+        graph.replay()
+        torch.cuda.synchronize()
+        got = u.clone()
+        assert torch.equal(got, g.vcycle(f, "c128")), k
