@@ -2095,44 +2095,45 @@ __device__ __forceinline__ double ilu_flip(double v, int mask)
 {
     return __hiloint2double(__double2hiint(v) ^ mask, __double2loint(v));
 }
+// the value of the lane before; lane 0 gets `first`
+__device__ __forceinline__ double ilu_before(double v, double first)
+{
+    const int lo = __builtin_amdgcn_update_dpp(__double2loint(first), __double2loint(v), 0x138, 0xF, 0xF, false);   // wave_shr:1
+    const int hi = __builtin_amdgcn_update_dpp(__double2hiint(first), __double2hiint(v), 0x138, 0xF, 0xF, false);
+    return __hiloint2double(hi, lo);
+}
 
-// LDS of the row form: two chunk buffers (factors, diagonal, right-hand
-// side) and the ring of solved values, rows -HR .. RW - 1 per step
-template <bool GAL> struct IluLds {
-    using S = IluSet<GAL>;
-    double2 fac[2][S::S * (S::NLO + 1) * S::RW];
-    double2 rhs[2][S::S * S::RW];
-    double2 ring[3 * S::S * (S::RW + S::HR) * S::XE];
-    int failed;
-};
-
-// One chunk of the solving wave, 25-point set.  lane = 2 row + part.
+// One chunk of the solving wave, 25-point set.  lane = 2 row + part; fac, rhs:
+// the chunk's LDS buffers, cur and prev the ring's slots of this chunk and the
+// one before.  A forward step starts with the terms that wait for nothing (k =
+// 0 .. 8); the backward order starts with the newest values.
 template <bool FWD>
-__device__ __forceinline__ void ilu_chunk(IluLds<true> &sm, int c, int row, int R, int nx, int d0, double *wst,
-                                          double2 (&W1)[6], double2 (&W2)[6], double2 (&O)[2])
+__device__ __forceinline__ void ilu_chunk(const double2 *fac, const double2 *rhs_, double2 *cur, const double2 *prev, int c,
+                                          int row, int R, int nx, double2 (&W1)[6], double2 (&W2)[6], double2 (&O)[2])
 {
     using S = IluSet<true>;
     constexpr int NF = FWD ? S::NLO : S::NLO + 1, ST = (S::RW + S::HR) * S::XE;
-    const int part = threadIdx.x & 1;
+    const int part = threadIdx.x & 1, rr = FWD ? row : (row < R ? R - 1 - row : 0);
     const int mneg = part == 0 ? (int)0x80000000 : 0, mdiv = part == 0 ? 0 : (int)0x80000000;
-    const double2 *fac = sm.fac[c & 1] + (FWD ? row : (row < R ? R - 1 - row : 0));
-    const double *rhs = (const double *)(sm.rhs[c & 1] + (FWD ? row : (row < R ? R - 1 - row : 0))) + part;
-    // ring entry of this row: rows -2, -1 lead; an entry is (x, -y, y, x)
-    double2 *cur = sm.ring + (c % 3) * S::S * ST + row * S::XE + part;
-    const double2 *prev = sm.ring + ((c + 2) % 3) * S::S * ST + row * S::XE + part;
-    const int i0 = (c - 1) * S::S - S::M * row;
+    const int i0 = (c - 1) * S::S - S::M * row, nxr = row < R ? nx : 0;
+    const double *rhs = (const double *)(rhs_ + rr) + part;
+    double2 *own = cur + (row + S::HR) * S::XE + part;      // ring entries are (x, -y), (y, x)
+    fac += rr;
 #pragma unroll
     for (int s = 0; s < S::S; ++s) {
-        const int i = i0 + s, ss = FWD ? s : S::S - 1 - s;
-        const bool act = (unsigned)i < (unsigned)nx && row < R;
-        W1[s] = (s >= 1 ? cur + (s - 1) * ST : prev + (S::S - 1) * ST)[1 * S::XE];
-        W2[s] = (s >= 4 ? cur + (s - 4) * ST : prev + (S::S + s - 4) * ST)[0];
+        const int ss = FWD ? s : S::S - 1 - s;
+        // row - 1's value of the step before (row -1's from the ring) and row
+        // - 2's of four steps before
+        const double2 o1 = O[(s + 1) & 1], o2 = O[s & 1];
+        const double2 h = (s >= 1 ? cur + (s - 1) * ST : prev + (S::S - 1) * ST)[(S::HR - 1) * S::XE + 1];
+        const double u = ilu_before(ilu_before(o1.x, h.x), h.y);
+        W1[s] = cmk<double>(u, ilu_flip(ilu_swap(u), mneg));
+        W2[s] = (s >= 4 ? cur + (s - 4) * ST : prev + (S::S + s - 4) * ST)[row * S::XE + part];
         double v = rhs[ss * S::RW * 2];
         auto term = [&](int k, double2 q) {
             const double2 f = fac[(ss * NF + (FWD ? k : 1 + k)) * S::RW];
             v = v - (f.x * q.x + f.y * q.y);
         };
-        const double2 o1 = O[(s + 1) & 1], o2 = O[s & 1];
         if (FWD) {
 #pragma unroll
             for (int k = 0; k < 5; ++k) term(k, W2[(s + 2 + k) % 6]);
@@ -2151,31 +2152,29 @@ __device__ __forceinline__ void ilu_chunk(IluLds<true> &sm, int c, int row, int 
             const double num = v * dg.x + ilu_flip(ilu_swap(v), mdiv) * dg.y;
             v = num / (dg.x * dg.x + dg.y * dg.y);
         }
-        v = act ? v : 0.0;
-        const double2 e = cmk<double>(v, ilu_flip(ilu_swap(v), mneg));
-        O[s & 1] = e;
-        (cur + s * ST)[S::HR * S::XE] = e;
-        if (act) ((HH_GLOBAL double *)wst)[(int64_t)(FWD ? d0 + (c - 1) * S::S + s : d0 - ((c - 1) * S::S + s)) * S::RW * 2] = v;
+        v = (unsigned)(i0 + s) < (unsigned)nxr ? v : 0.0;
+        O[s & 1] = cmk<double>(v, ilu_flip(ilu_swap(v), mneg));
+        own[s * ST] = O[s & 1];
     }
 }
 
 // One chunk of the solving wave, 5-point set.  lane = row.
 template <bool FWD>
-__device__ __forceinline__ void ilu_chunk(IluLds<false> &sm, int c, int row, int R, int nx, int d0, double *wst,
-                                          double2 &O)
+__device__ __forceinline__ void ilu_chunk(const double2 *fac, const double2 *rhs, double2 *cur, const double2 *prev, int c,
+                                          int row, int R, int nx, double2 &O)
 {
     using S = IluSet<false>;
     constexpr int NF = FWD ? S::NLO : S::NLO + 1, ST = (S::RW + S::HR) * S::XE;
     const int rr = FWD ? row : (row < R ? R - 1 - row : 0);
-    const double2 *fac = sm.fac[c & 1] + rr, *rhs = sm.rhs[c & 1] + rr;
-    double2 *cur = sm.ring + (c % 3) * S::S * ST + row;
-    const double2 *prev = sm.ring + ((c + 2) % 3) * S::S * ST + row;
-    const int i0 = (c - 1) * S::S - row;
+    const int i0 = (c - 1) * S::S - row, nxr = row < R ? nx : 0;
+    double2 *own = cur + row + S::HR;
+    fac += rr;
+    rhs += rr;
 #pragma unroll
     for (int s = 0; s < S::S; ++s) {
-        const int i = i0 + s, ss = FWD ? s : S::S - 1 - s;
-        const bool act = (unsigned)i < (unsigned)nx && row < R;
-        const double2 q = (s >= 1 ? cur + (s - 1) * ST : prev + (S::S - 1) * ST)[0];
+        const int ss = FWD ? s : S::S - 1 - s;
+        const double2 h = (s >= 1 ? cur + (s - 1) * ST : prev + (S::S - 1) * ST)[0];
+        const double2 q = cmk<double>(ilu_before(O.x, h.x), ilu_before(O.y, h.y));
         double2 v = rhs[ss * S::RW];
         const double2 *f = fac + ss * NF * S::RW;
         if (FWD) {
@@ -2186,23 +2185,34 @@ __device__ __forceinline__ void ilu_chunk(IluLds<false> &sm, int c, int row, int
             v = csub<double>(v, cmul<double>(f[2 * S::RW], q));
             v = cdiv<double>(v, f[0]);
         }
-        v.x = act ? v.x : 0.0;
-        v.y = act ? v.y : 0.0;
-        O = v;
-        (cur + s * ST)[S::HR] = v;
-        if (act) stg((double2 *)wst, (int64_t)(FWD ? d0 + (c - 1) * S::S + s : d0 - ((c - 1) * S::S + s)) * S::RW, v);
+        const bool act = (unsigned)(i0 + s) < (unsigned)nxr;
+        O = cmk<double>(act ? v.x : 0.0, act ? v.y : 0.0);
+        own[s * ST] = O;
     }
 }
 
+// LDS of the row form, arrays of their own (so that the factor reads need not
+// wait for the ring writes): two chunk buffers of factors and of right-hand
+// sides, and the ring of solved values, rows -HR .. RW - 1 per step
+template <bool GAL> struct IluLdsSize {
+    using S = IluSet<GAL>;
+    static constexpr int FAC = S::S * (S::NLO + 1) * S::RW, RHS = S::S * S::RW, ROW = (S::RW + S::HR) * S::XE, RING = 3 * S::S * ROW;
+};
+struct IluLds {
+    double2 *fac, *rhs, *ring;
+    int *failed;
+};
+
 // Stage b of one solve.
 template <bool GAL, bool FWD>
-__device__ __forceinline__ void ilu_stage(IluLds<GAL> &sm, const IluArgs &a, const IluLayout<GAL> &lay, int b, uint32_t epoch)
+__device__ __forceinline__ void ilu_stage(const IluLds &sm, const IluArgs &a, const IluLayout<GAL> &lay, int b, uint32_t epoch)
 {
     using S = IluSet<GAL>;
     constexpr int NF = FWD ? S::NLO : S::NLO + 1;           // factor entries per point and step
     constexpr int NL = 3 * 64, LF = S::S * NF * S::RW / NL, LW = S::S * S::RW / NL;   // loads per feeding thread
     static_assert(S::S * NF * S::RW % NL == 0 && S::S * S::RW % NL == 0, "a chunk is whole loads of the feeding waves");
-    constexpr int ST = (S::RW + S::HR) * S::XE;
+    using Z = IluLdsSize<GAL>;
+    constexpr int ST = Z::ROW;
     const int nx = lay.nx, R = lay.j0(b + 1) - lay.j0(b), nd = nx + S::M * (R - 1);
     const int64_t D0 = lay.d0(b);
     // chunk c covers steps (c - 1) S .. c S - 1: chunk 0 only fills the
@@ -2213,16 +2223,15 @@ __device__ __forceinline__ void ilu_stage(IluLds<GAL> &sm, const IluArgs &a, con
     __syncthreads();
     if (wave == 0) {
         const int row = GAL ? lane >> 1 : lane;
-        // this lane's place in w at step 0 (backward: of forward step nd - 1)
-        const int rr = FWD ? row : (row < R ? R - 1 - row : 0);
-        double *wst = (double *)(a.fl.w + D0 * S::RW + rr) + (GAL ? (lane & 1) : 0);
-        const int d0 = FWD ? 0 : nd - 1;
         const double2 zero = cmk<double>(0.0, 0.0);
         double2 W1[6] = {zero, zero, zero, zero, zero, zero}, W2[6] = {zero, zero, zero, zero, zero, zero}, O[2] = {zero, zero};
         for (int c = 0; c < nch; ++c) {
             __syncthreads();
-            if constexpr (GAL) ilu_chunk<FWD>(sm, c, row, R, nx, d0, wst, W1, W2, O);
-            else ilu_chunk<FWD>(sm, c, row, R, nx, d0, wst, O[0]);
+            const double2 *fac = sm.fac + (c & 1) * Z::FAC, *rhs = sm.rhs + (c & 1) * Z::RHS;
+            double2 *cur = sm.ring + (c % 3) * S::S * ST;
+            const double2 *prev = sm.ring + ((c + 2) % 3) * S::S * ST;
+            if constexpr (GAL) ilu_chunk<FWD>(fac, rhs, cur, prev, c, row, R, nx, W1, W2, O);
+            else ilu_chunk<FWD>(fac, rhs, cur, prev, c, row, R, nx, O[0]);
         }
         __syncthreads();
     } else {
@@ -2263,8 +2272,8 @@ __device__ __forceinline__ void ilu_stage(IluLds<GAL> &sm, const IluArgs &a, con
                 if (!__any(!ok)) break;
                 // a stage before that never comes (it cannot, with every
                 // workgroup resident) ends as NaN instead of a hang
-                if (n >= (sm.failed ? 0 : HH_ILU_SPIN)) {
-                    sm.failed = 1;
+                if (n >= (*sm.failed ? 0 : HH_ILU_SPIN)) {
+                    *sm.failed = 1;
                     break;
                 }
             }
@@ -2288,6 +2297,16 @@ __device__ __forceinline__ void ilu_stage(IluLds<GAL> &sm, const IluArgs &a, con
                 __hip_atomic_store(ch + b * cw + (int64_t)col * (S::HR * 4), v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             }
         };
+        // chunk c's solved values from the ring to w
+        auto store = [&](int c) {
+            double2 *w = a.fl.w + (D0 + (FWD ? 0 : nd - 1)) * S::RW;
+            for (int e = lane; e < S::S * S::RW; e += 64) {
+                const int s = e / S::RW, row = e % S::RW, d = (c - 1) * S::S + s, i = d - S::M * row;
+                const double2 *x = sm.ring + ((c % 3) * S::S + s) * ST + (row + S::HR) * S::XE;
+                const double2 v = cmk<double>(x[0].x, GAL ? x[1].x : x[0].y);
+                if (row < R && i >= 0 && i < nx) stg(w, FWD ? (int64_t)d * S::RW + row : -(int64_t)d * S::RW + (R - 1 - row), v);
+            }
+        };
 #pragma unroll
         for (int u = 0; u < 3; ++u) fetch(1 + u, q[u]);
         if (wave == 1) poll(0);
@@ -2296,7 +2315,7 @@ __device__ __forceinline__ void ilu_stage(IluLds<GAL> &sm, const IluArgs &a, con
             for (int u = 0; u < 3; ++u) {
                 const int c = c0 + u;
                 __syncthreads();
-                double2 *f = sm.fac[(c + 1) & 1] + ft, *w = sm.rhs[(c + 1) & 1] + ft;
+                double2 *f = sm.fac + ((c + 1) & 1) * Z::FAC + ft, *w = sm.rhs + ((c + 1) & 1) * Z::RHS + ft;
 #pragma unroll
                 for (int m = 0; m < LF; ++m) f[m * NL] = q[u][m];
 #pragma unroll
@@ -2304,10 +2323,12 @@ __device__ __forceinline__ void ilu_stage(IluLds<GAL> &sm, const IluArgs &a, con
                 fetch(c + 4, q[u]);
                 if (wave == 1) poll(c + 1);
                 if (wave == 2 && c > 0) publish(c - 1);
+                if (wave == 3 && c > 0) store(c - 1);
             }
         }
         __syncthreads();
         if (wave == 2) publish(nch - 1);
+        if (wave == 3) store(nch - 1);
     }
     __syncthreads();
 }
@@ -2315,11 +2336,16 @@ __device__ __forceinline__ void ilu_stage(IluLds<GAL> &sm, const IluArgs &a, con
 template <bool GAL>
 __global__ __launch_bounds__(HH_ILU_ROWS_WG, 1) void k_ilu_up_rows(Ctx cx, IluArgs a)
 {
-    __shared__ IluLds<GAL> sm;
+    using Z = IluLdsSize<GAL>;
+    __shared__ double2 fac[2 * Z::FAC];
+    __shared__ double2 rhs[2 * Z::RHS];
+    __shared__ double2 ring[Z::RING];
+    __shared__ int failed;
     if (phase_of(cx, 0) != PH_RUN) return;
+    const IluLds sm{fac, rhs, ring, &failed};
     const IluLayout<GAL> lay(a.fl.n[0], a.fl.n[1]);
     const uint32_t epoch = (uint32_t)a.chan[0];
-    if (threadIdx.x == 0) sm.failed = 0;
+    if (threadIdx.x == 0) failed = 0;
     const int g = (int)blockIdx.x, G = (int)gridDim.x;
     int b = g;
     for (; b < lay.nb; b += G) ilu_stage<GAL, true>(sm, a, lay, b, epoch);

@@ -88,20 +88,22 @@ def run_stage(K, lay, b, fwd, channel, solved):
         published = publish(c - 1) if c else set()
         new = c + 1
         reads, writes = set(), set()
+        stored = {((c - 1) % 3 * S + s, row + HR) for s in range(S) for row in range(RW)}   # chunk c - 1 on its way to w
         for s in range(S):
             d = (c - 1) * S + s
             vals = {}
+            last = [O[row][(s + 1) & 1 if M == 3 else 0] for row in range(RW)]     # every row's value of step d - 1
             for row in range(RW):
                 i = d - M * row
                 act = 0 <= i < nx and row < R
                 r1 = ((c % 3) * S + s - 1) if s >= 1 else (((c + 2) % 3) * S + S - 1)
                 r2 = ((c % 3) * S + s - 4) if s >= 4 else (((c + 2) % 3) * S + S + s - 4)
+                # row - 1's value of step d - 1 from the lane before, row -1's from the ring
+                q1 = last[row - 1] if row else ring[r1][HR - 1]
+                reads.add((r1, HR - 1))
                 if M == 3:
-                    W1[row][s], W2[row][s] = ring[r1][row + 1], ring[r2][row]
-                    reads |= {(r1, row + 1), (r2, row)}
-                else:
-                    q1 = ring[r1][row]
-                    reads.add((r1, row))
+                    W1[row][s], W2[row][s] = q1, ring[r2][row]
+                    reads.add((r2, row))
                 if act:
                     slot = s if fwd else S - 1 - s
                     rr = row if fwd else R - 1 - row
@@ -132,7 +134,7 @@ def run_stage(K, lay, b, fwd, channel, solved):
                     O[row][0] = vals[row]
                 if vals[row]:
                     solved.add((fwd, vals[row]))
-        assert not polled & (reads | writes) and not published & writes
+        assert not polled & (reads | writes | stored) and not (published | stored) & writes
         bufs[new & 1] = fetch(K, fwd, nd, new, NF)
         fetch(K, fwd, nd, c + 4, NF)
     publish(nch - 1)
