@@ -1860,7 +1860,7 @@ template <> struct IluSet<true> {
     __host__ __device__ static constexpr int up(int k) { return 13 + k; }     // s = 13 .. 24
 };
 template <> struct IluSet<false> {
-    static constexpr int M = 1, NLO = 2, RW = 64, HR = 1, S = 12, XE = 1;
+    static constexpr int M = 1, NLO = 2, RW = 64, HR = 1, S = 6, XE = 1;
     __host__ __device__ static constexpr int lo(int k) { return k == 0 ? 7 : 11; }
     __host__ __device__ static constexpr int up(int k) { return k == 0 ? 13 : 17; }
 };
@@ -2090,7 +2090,12 @@ __global__ __launch_bounds__(HH_ILU_WG) void k_ilu_up(Ctx cx, IluArgs a)
 // Values and operation order are k_ilu_up's: a product f q is taken as
 // (f.x a + f.y b) with (a, b) = (q.x, -q.y) resp. (q.y, q.x), which rounds as
 // cmul does; values outside the grid are +0 and their factors +0.
-__device__ __forceinline__ double ilu_swap(double v) { return dpp_x<0xB1>(v); }   // the other lane of a row's pair
+// the other lane of a row's pair (every lane has one, so no old value is kept)
+__device__ __forceinline__ double ilu_swap(double v)
+{
+    return __hiloint2double(__builtin_amdgcn_mov_dpp(__double2hiint(v), 0xB1, 0xF, 0xF, true),
+                            __builtin_amdgcn_mov_dpp(__double2loint(v), 0xB1, 0xF, 0xF, true));
+}
 __device__ __forceinline__ double ilu_flip(double v, int mask)
 {
     return __hiloint2double(__double2hiint(v) ^ mask, __double2loint(v));
@@ -2103,92 +2108,98 @@ __device__ __forceinline__ double ilu_before(double v, double first)
     return __hiloint2double(hi, lo);
 }
 
-// One chunk of the solving wave, 25-point set.  lane = 2 row + part; fac, rhs:
-// the chunk's LDS buffers, cur and prev the ring's slots of this chunk and the
-// one before.  A forward step starts with the terms that wait for nothing (k =
-// 0 .. 8); the backward order starts with the newest values.
+// What a step of the solving wave reads from LDS one step ahead: the point's
+// factors and right-hand side, row - 2's value of four steps before (25-point
+// set) or row -1's of the step before (5-point set).
+template <bool GAL, bool FWD> struct IluStep;
+template <bool FWD> struct IluStep<true, FWD> {
+    using S = IluSet<true>;
+    double2 f[S::NLO], dg, w2;
+    double r;
+};
+template <bool FWD> struct IluStep<false, FWD> {
+    using S = IluSet<false>;
+    double2 f[S::NLO], dg, h, r;
+};
+// step s of the chunk with buffers fac, rhs and ring slots cur, prev (row rr
+// of the buffers; lane addresses include the part)
 template <bool FWD>
-__device__ __forceinline__ void ilu_chunk(const double2 *fac, const double2 *rhs_, double2 *cur, const double2 *prev, int c,
-                                          int row, int R, int nx, double2 (&W1)[6], double2 (&W2)[6], double2 (&O)[2])
+__device__ __forceinline__ void ilu_load(IluStep<true, FWD> &q, const double2 *fac, const double2 *rhs, const double2 *cur,
+                                         const double2 *prev, int s, int rr, int row, int part)
 {
     using S = IluSet<true>;
     constexpr int NF = FWD ? S::NLO : S::NLO + 1, ST = (S::RW + S::HR) * S::XE;
-    const int part = threadIdx.x & 1, rr = FWD ? row : (row < R ? R - 1 - row : 0);
-    const int mneg = part == 0 ? (int)0x80000000 : 0, mdiv = part == 0 ? 0 : (int)0x80000000;
-    const int i0 = (c - 1) * S::S - S::M * row, nxr = row < R ? nx : 0;
-    const double *rhs = (const double *)(rhs_ + rr) + part;
-    double2 *own = cur + (row + S::HR) * S::XE + part;      // ring entries are (x, -y), (y, x)
-    fac += rr;
+    const int ss = FWD ? s : S::S - 1 - s;
+    q.w2 = (s >= 4 ? cur + (s - 4) * ST : prev + (S::S + s - 4) * ST)[row * S::XE + part];
+    q.r = ((const double *)(rhs + ss * S::RW + rr))[part];
 #pragma unroll
-    for (int s = 0; s < S::S; ++s) {
-        const int ss = FWD ? s : S::S - 1 - s;
-        // row - 1's value of the step before (row -1's from the ring) and row
-        // - 2's of four steps before
-        const double2 o1 = O[(s + 1) & 1], o2 = O[s & 1];
-        const double2 h = (s >= 1 ? cur + (s - 1) * ST : prev + (S::S - 1) * ST)[(S::HR - 1) * S::XE + 1];
-        const double u = ilu_before(ilu_before(o1.x, h.x), h.y);
-        W1[s] = cmk<double>(u, ilu_flip(ilu_swap(u), mneg));
-        W2[s] = (s >= 4 ? cur + (s - 4) * ST : prev + (S::S + s - 4) * ST)[row * S::XE + part];
-        double v = rhs[ss * S::RW * 2];
-        auto term = [&](int k, double2 q) {
-            const double2 f = fac[(ss * NF + (FWD ? k : 1 + k)) * S::RW];
-            v = v - (f.x * q.x + f.y * q.y);
-        };
-        if (FWD) {
-#pragma unroll
-            for (int k = 0; k < 5; ++k) term(k, W2[(s + 2 + k) % 6]);
-#pragma unroll
-            for (int k = 0; k < 5; ++k) term(5 + k, W1[(s + 2 + k) % 6]);
-            term(10, o2);
-            term(11, o1);
-        } else {
-            term(0, o1);
-            term(1, o2);
-#pragma unroll
-            for (int k = 0; k < 5; ++k) term(2 + k, W1[(s + 6 - k) % 6]);
-#pragma unroll
-            for (int k = 0; k < 5; ++k) term(7 + k, W2[(s + 6 - k) % 6]);
-            const double2 dg = fac[ss * NF * S::RW];
-            const double num = v * dg.x + ilu_flip(ilu_swap(v), mdiv) * dg.y;
-            v = num / (dg.x * dg.x + dg.y * dg.y);
-        }
-        v = (unsigned)(i0 + s) < (unsigned)nxr ? v : 0.0;
-        O[s & 1] = cmk<double>(v, ilu_flip(ilu_swap(v), mneg));
-        own[s * ST] = O[s & 1];
-    }
+    for (int k = 0; k < S::NLO; ++k) q.f[k] = fac[(ss * NF + (FWD ? k : 1 + k)) * S::RW + rr];
+    if (!FWD) q.dg = fac[ss * NF * S::RW + rr];
 }
-
-// One chunk of the solving wave, 5-point set.  lane = row.
 template <bool FWD>
-__device__ __forceinline__ void ilu_chunk(const double2 *fac, const double2 *rhs, double2 *cur, const double2 *prev, int c,
-                                          int row, int R, int nx, double2 &O)
+__device__ __forceinline__ void ilu_load(IluStep<false, FWD> &q, const double2 *fac, const double2 *rhs, const double2 *cur,
+                                         const double2 *prev, int s, int rr, int, int)
 {
     using S = IluSet<false>;
     constexpr int NF = FWD ? S::NLO : S::NLO + 1, ST = (S::RW + S::HR) * S::XE;
-    const int rr = FWD ? row : (row < R ? R - 1 - row : 0);
-    const int i0 = (c - 1) * S::S - row, nxr = row < R ? nx : 0;
-    double2 *own = cur + row + S::HR;
-    fac += rr;
-    rhs += rr;
+    const int ss = FWD ? s : S::S - 1 - s;
+    q.h = (s >= 1 ? cur + (s - 1) * ST : prev + (S::S - 1) * ST)[0];
+    q.r = rhs[ss * S::RW + rr];
 #pragma unroll
-    for (int s = 0; s < S::S; ++s) {
-        const int ss = FWD ? s : S::S - 1 - s;
-        const double2 h = (s >= 1 ? cur + (s - 1) * ST : prev + (S::S - 1) * ST)[0];
-        const double2 q = cmk<double>(ilu_before(O.x, h.x), ilu_before(O.y, h.y));
-        double2 v = rhs[ss * S::RW];
-        const double2 *f = fac + ss * NF * S::RW;
-        if (FWD) {
-            v = csub<double>(v, cmul<double>(f[0], q));
-            v = csub<double>(v, cmul<double>(f[S::RW], O));
-        } else {
-            v = csub<double>(v, cmul<double>(f[S::RW], O));
-            v = csub<double>(v, cmul<double>(f[2 * S::RW], q));
-            v = cdiv<double>(v, f[0]);
-        }
-        const bool act = (unsigned)(i0 + s) < (unsigned)nxr;
-        O = cmk<double>(act ? v.x : 0.0, act ? v.y : 0.0);
-        own[s * ST] = O;
+    for (int k = 0; k < S::NLO; ++k) q.f[k] = fac[(ss * NF + (FWD ? k : 1 + k)) * S::RW + rr];
+    if (!FWD) q.dg = fac[ss * NF * S::RW + rr];
+}
+
+// One step, 25-point set: lane = 2 row + part; i the row's column, nxr = nx
+// (0 past the stage's last row).  W1, W2: the last values of rows - 1 and - 2
+// by step mod 6 (w1 the newest), O the row's own by step mod 2.
+template <bool FWD>
+__device__ __forceinline__ void ilu_step(const IluStep<true, FWD> &q, double2 w1, int s, int i, int nxr, int part,
+                                         double2 (&W1)[6], double2 (&W2)[6], double2 (&O)[2])
+{
+    const int mneg = part == 0 ? (int)0x80000000 : 0, mdiv = part == 0 ? 0 : (int)0x80000000;
+    const double2 o1 = O[(s + 1) & 1], o2 = O[s & 1];
+    W1[s] = w1;
+    W2[s] = q.w2;
+    double v = q.r;
+    auto term = [&](int k, double2 w) { v = v - (q.f[k].x * w.x + q.f[k].y * w.y); };
+    if (FWD) {
+#pragma unroll
+        for (int k = 0; k < 5; ++k) term(k, W2[(s + 2 + k) % 6]);
+#pragma unroll
+        for (int k = 0; k < 5; ++k) term(5 + k, W1[(s + 2 + k) % 6]);
+        term(10, o2);
+        term(11, o1);
+    } else {
+        term(0, o1);
+        term(1, o2);
+#pragma unroll
+        for (int k = 0; k < 5; ++k) term(2 + k, W1[(s + 6 - k) % 6]);
+#pragma unroll
+        for (int k = 0; k < 5; ++k) term(7 + k, W2[(s + 6 - k) % 6]);
+        const double num = v * q.dg.x + ilu_flip(ilu_swap(v), mdiv) * q.dg.y;
+        v = num / (q.dg.x * q.dg.x + q.dg.y * q.dg.y);
     }
+    v = (unsigned)i < (unsigned)nxr ? v : 0.0;
+    O[s & 1] = cmk<double>(v, ilu_flip(ilu_swap(v), mneg));
+}
+// One step, 5-point set: lane = row.
+template <bool FWD>
+__device__ __forceinline__ void ilu_step(const IluStep<false, FWD> &q, double2, int, int i, int nxr, int, double2 (&)[6],
+                                         double2 (&)[6], double2 (&O)[2])
+{
+    const double2 b = cmk<double>(ilu_before(O[0].x, q.h.x), ilu_before(O[0].y, q.h.y));
+    double2 v = q.r;
+    if (FWD) {
+        v = csub<double>(v, cmul<double>(q.f[0], b));
+        v = csub<double>(v, cmul<double>(q.f[1], O[0]));
+    } else {
+        v = csub<double>(v, cmul<double>(q.f[0], O[0]));
+        v = csub<double>(v, cmul<double>(q.f[1], b));
+        v = cdiv<double>(v, q.dg);
+    }
+    const bool act = (unsigned)i < (unsigned)nxr;
+    O[0] = cmk<double>(act ? v.x : 0.0, act ? v.y : 0.0);
 }
 
 // LDS of the row form, arrays of their own (so that the factor reads need not
@@ -2222,16 +2233,36 @@ __device__ __forceinline__ void ilu_stage(const IluLds &sm, const IluArgs &a, co
     for (int t = threadIdx.x; t < 3 * S::S * ST; t += HH_ILU_ROWS_WG) sm.ring[t] = cmk<double>(0.0, 0.0);
     __syncthreads();
     if (wave == 0) {
-        const int row = GAL ? lane >> 1 : lane;
+        const int row = GAL ? lane >> 1 : lane, part = GAL ? lane & 1 : 0;
+        const int rr = FWD ? row : (row < R ? R - 1 - row : 0);
+        int nxr = row < R ? nx : 0;
+        asm("" : "+v"(nxr));     // one compare per step, not two
         const double2 zero = cmk<double>(0.0, 0.0);
         double2 W1[6] = {zero, zero, zero, zero, zero, zero}, W2[6] = {zero, zero, zero, zero, zero, zero}, O[2] = {zero, zero};
+        IluStep<GAL, FWD> q[2];
+        ilu_load<FWD>(q[0], sm.fac, sm.rhs, sm.ring, sm.ring, 0, rr, row, part);   // chunk 0 solves no point
+        int b0 = 0;
         for (int c = 0; c < nch; ++c) {
             __syncthreads();
-            const double2 *fac = sm.fac + (c & 1) * Z::FAC, *rhs = sm.rhs + (c & 1) * Z::RHS;
-            double2 *cur = sm.ring + (c % 3) * S::S * ST;
-            const double2 *prev = sm.ring + ((c + 2) % 3) * S::S * ST;
-            if constexpr (GAL) ilu_chunk<FWD>(fac, rhs, cur, prev, c, row, R, nx, W1, W2, O);
-            else ilu_chunk<FWD>(fac, rhs, cur, prev, c, row, R, nx, O[0]);
+            const int b1 = b0 == 2 ? 0 : b0 + 1, b2 = 3 - b0 - b1;    // c, c + 1, c - 1 mod 3
+            double2 *cur = sm.ring + b0 * (S::S * ST);
+            const double2 *prev = sm.ring + b2 * (S::S * ST);
+            const double2 *fac = sm.fac + b0 * Z::FAC, *rhs = sm.rhs + b0 * Z::RHS;
+            const int i0 = (c - 1) * S::S - S::M * row;
+#pragma unroll
+            for (int s = 0; s < S::S; ++s) {
+                // row - 1's value of the step before (25-point set): written to
+                // the ring a moment ago, back before its term's turn
+                double2 w1 = zero;
+                if (GAL) w1 = (s >= 1 ? cur + (s - 1) * ST : prev + (S::S - 1) * ST)[(row + 1) * S::XE + part];
+                if (s + 1 < S::S) ilu_load<FWD>(q[(s + 1) & 1], fac, rhs, cur, prev, s + 1, rr, row, part);
+                else ilu_load<FWD>(q[0], sm.fac + b1 * Z::FAC, sm.rhs + b1 * Z::RHS, sm.ring + b1 * (S::S * ST), cur, 0, rr, row, part);
+                __builtin_amdgcn_sched_barrier(0);
+                ilu_step<FWD>(q[s & 1], w1, s, i0 + s, nxr, part, W1, W2, O);
+                cur[s * ST + (row + S::HR) * S::XE + part] = O[GAL ? s & 1 : 0];
+                __builtin_amdgcn_sched_barrier(0);
+            }
+            b0 = b1;
         }
         __syncthreads();
     } else {
@@ -2258,18 +2289,27 @@ __device__ __forceinline__ void ilu_stage(const IluLds &sm, const IluArgs &a, co
         const int64_t cw = (int64_t)nx * S::HR * 4;      // words per stage
         uint64_t *ch = a.chan + 1 + (FWD ? 0 : lay.nb * cw) + (h * 4 + part * 2 + half);
         const bool first = FWD ? b == 0 : b == lay.nb - 1;
-        auto poll = [&](int c) {
+        // the item's place for chunk c, null where the rows above are not there
+        auto item = [&](int c) -> const uint64_t * {
             const int col = (c - 1) * S::S + is + S::M * (1 + h);
             const bool need = !first && lane < NI && col >= 0 && col < nx;
-            const uint64_t *p = ch + (FWD ? b - 1 : b + 1) * cw + (int64_t)(need ? col : 0) * (S::HR * 4);
-            uint64_t v = 0;
-            bool ok = !need;
-            for (int n = 0;; ++n) {
+            return need ? ch + (FWD ? b - 1 : b + 1) * cw + (int64_t)col * (S::HR * 4) : nullptr;
+        };
+        auto look = [&](int c) -> uint64_t {
+            const uint64_t *p = item(c);
+            return __hip_atomic_load(p ? p : ch, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        };
+        // chunk c's rows above into the ring; v: the items as they were seen
+        // some chunks ago, looked up again until all are there
+        auto poll = [&](int c, uint64_t v) {
+            const uint64_t *p = item(c);
+            const bool need = p != nullptr;
+            bool ok = !need || (int)((uint32_t)(v >> 32) - epoch) >= 0;
+            for (int n = 0; __any(!ok); ++n) {
                 if (!ok) {
                     v = __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                     ok = (int)((uint32_t)(v >> 32) - epoch) >= 0;
                 }
-                if (!__any(!ok)) break;
                 // a stage before that never comes (it cannot, with every
                 // workgroup resident) ends as NaN instead of a hang
                 if (n >= (*sm.failed ? 0 : HH_ILU_SPIN)) {
@@ -2277,6 +2317,7 @@ __device__ __forceinline__ void ilu_stage(const IluLds &sm, const IluArgs &a, co
                     break;
                 }
             }
+            if (!need) v = 0;
             uint32_t w = (uint32_t)v;
             if (need && !ok) w = half ? 0x7ff80000u : 0u;
             if (lane < NI) {
@@ -2307,21 +2348,36 @@ __device__ __forceinline__ void ilu_stage(const IluLds &sm, const IluArgs &a, co
                 if (row < R && i >= 0 && i < nx) stg(w, FWD ? (int64_t)d * S::RW + row : -(int64_t)d * S::RW + (R - 1 - row), v);
             }
         };
+        // chunk c's loads to its LDS buffer
+        auto fill = [&](int c, const double2(&v)[LF + LW]) {
+            double2 *f = sm.fac + (c % 3) * Z::FAC + ft, *w = sm.rhs + (c % 3) * Z::RHS + ft;
 #pragma unroll
-        for (int u = 0; u < 3; ++u) fetch(1 + u, q[u]);
-        if (wave == 1) poll(0);
+            for (int m = 0; m < LF; ++m) f[m * NL] = v[m];
+#pragma unroll
+            for (int m = 0; m < LW; ++m) w[m * NL] = v[LF + m];
+        };
+        fetch(1, q[0]);
+        fetch(2, q[1]);
+        fetch(3, q[2]);
+        fill(1, q[0]);
+        fetch(4, q[0]);
+        uint64_t seen[3] = {0, 0, 0};
+        if (wave == 1) {
+            poll(0, look(0));
+#pragma unroll
+            for (int u = 0; u < 3; ++u) seen[u] = look(1 + u);
+        }
         for (int c0 = 0; c0 < nch; c0 += 3) {
 #pragma unroll
             for (int u = 0; u < 3; ++u) {
                 const int c = c0 + u;
                 __syncthreads();
-                double2 *f = sm.fac + ((c + 1) & 1) * Z::FAC + ft, *w = sm.rhs + ((c + 1) & 1) * Z::RHS + ft;
-#pragma unroll
-                for (int m = 0; m < LF; ++m) f[m * NL] = q[u][m];
-#pragma unroll
-                for (int m = 0; m < LW; ++m) w[m * NL] = q[u][LF + m];
-                fetch(c + 4, q[u]);
-                if (wave == 1) poll(c + 1);
+                fill(c + 2, q[(u + 1) % 3]);
+                fetch(c + 5, q[(u + 1) % 3]);
+                if (wave == 1) {
+                    poll(c + 1, seen[u]);
+                    seen[u] = look(c + 4);
+                }
                 if (wave == 2 && c > 0) publish(c - 1);
                 if (wave == 3 && c > 0) store(c - 1);
             }
@@ -2337,8 +2393,8 @@ template <bool GAL>
 __global__ __launch_bounds__(HH_ILU_ROWS_WG, 1) void k_ilu_up_rows(Ctx cx, IluArgs a)
 {
     using Z = IluLdsSize<GAL>;
-    __shared__ double2 fac[2 * Z::FAC];
-    __shared__ double2 rhs[2 * Z::RHS];
+    __shared__ double2 fac[3 * Z::FAC];
+    __shared__ double2 rhs[3 * Z::RHS];
     __shared__ double2 ring[Z::RING];
     __shared__ int failed;
     if (phase_of(cx, 0) != PH_RUN) return;

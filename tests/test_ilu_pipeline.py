@@ -1,15 +1,15 @@
 """CPU model of the ILU(0) row form's pipeline (k_ilu_up_rows, IluLayout),
 written from its index arithmetic: stages of at most RW rows, chunks of S
 steps between barriers, the LDS ring of three chunks with the rows of the
-stage before in front, the register windows, the two chunk buffers with loads
-three chunks ahead, and the channel by column.  Values are replaced by the
+stage before in front, the register windows, the three chunk buffers filled
+two chunks ahead and read one step ahead, and the channel by column.  Values are replaced by the
 point they belong to, so every read is checked to be the neighbour that the
 stencil asks for, and within a chunk nothing is written that another wave
 reads."""
 import pytest
 
 GAL = {"M": 3, "RW": 32, "HR": 2, "S": 6, "NLO": 12, "lo": list(range(12)), "up": list(range(13, 25))}
-FIVE = {"M": 1, "RW": 64, "HR": 1, "S": 12, "NLO": 2, "lo": [7, 11], "up": [13, 17]}
+FIVE = {"M": 1, "RW": 64, "HR": 1, "S": 6, "NLO": 2, "lo": [7, 11], "up": [13, 17]}
 
 
 class Layout:
@@ -81,16 +81,21 @@ def run_stage(K, lay, b, fwd, channel, solved):
         return slots
 
     poll(0)
-    bufs = [None, None]
+    bufs = [None, fetch(K, fwd, nd, 1, NF), None]
     for c in range(nch):
-        # feeding waves, beside the solving wave: chunk c + 1 into the other buffer
+        # feeding waves, beside the solving wave
         polled = poll(c + 1)
         published = publish(c - 1) if c else set()
-        new = c + 1
         reads, writes = set(), set()
         stored = {((c - 1) % 3 * S + s, row + HR) for s in range(S) for row in range(RW)}   # chunk c - 1 on its way to w
         for s in range(S):
             d = (c - 1) * S + s
+            if s == 0:
+                ahead = nxt if c else None     # step 0 was read at the end of the chunk before
+            else:
+                ahead = bufs[c % 3]
+            if s == S - 1:
+                nxt = bufs[(c + 1) % 3]
             vals = {}
             last = [O[row][(s + 1) & 1 if M == 3 else 0] for row in range(RW)]     # every row's value of step d - 1
             for row in range(RW):
@@ -107,7 +112,7 @@ def run_stage(K, lay, b, fwd, channel, solved):
                 if act:
                     slot = s if fwd else S - 1 - s
                     rr = row if fwd else R - 1 - row
-                    step, place = bufs[c & 1][(slot * NF) * RW + rr]
+                    step, place = ahead[(slot * NF) * RW + rr]
                     assert (step, place) == ((d if fwd else nd - 1 - d), rr)
                     if M == 3:
                         o1, o2 = O[row][(s + 1) & 1], O[row][s & 1]
@@ -135,8 +140,8 @@ def run_stage(K, lay, b, fwd, channel, solved):
                 if vals[row]:
                     solved.add((fwd, vals[row]))
         assert not polled & (reads | writes | stored) and not (published | stored) & writes
-        bufs[new & 1] = fetch(K, fwd, nd, new, NF)
-        fetch(K, fwd, nd, c + 4, NF)
+        bufs[(c + 2) % 3] = fetch(K, fwd, nd, c + 2, NF)     # beside the solving wave: another buffer than c's and c + 1's
+        fetch(K, fwd, nd, c + 5, NF)
     publish(nch - 1)
 
 
