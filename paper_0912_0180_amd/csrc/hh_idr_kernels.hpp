@@ -23,17 +23,11 @@
 
 namespace hh {
 
-__device__ int idr_nvals(const ProbDev *pd, int kind)
-{
-    const SolveState *st = pd->st;
-    if (kind == FIN_IDR_OMEGA) return 3;
-    if (kind == FIN_IDR_STEP) return st->startup >= 0 ? 1 + 4 * HH_MAX_S : 1 + 2 * st->s;
-    return 1;
-}
-
 // s x s complex LU solve G c = m (G row major), same algorithm as the host
-// setup's dense LU.  Returns false for an exactly singular pivot.
-__device__ bool small_solve(const double2 *Gin, int s, const double2 *m, double2 *c)
+// setup's dense LU.  Returns false for an exactly singular pivot.  One thread,
+// in LDS; for s <= 4 in registers (S = s, rows swapped by selects), where it
+// takes about 2 us instead of waiting for LDS between dependent steps.
+__device__ inline bool small_solve_lds(const double2 *Gin, int s, const double2 *m, double2 *c)
 {
     __shared__ double2 A[HH_MAX_S * HH_MAX_S];   // thread 0 only (keeps the solve out of scratch memory)
     __shared__ int perm[HH_MAX_S];
@@ -79,8 +73,78 @@ __device__ bool small_solve(const double2 *Gin, int s, const double2 *m, double2
     }
     return true;
 }
+template <int S> __device__ inline bool small_solve_reg(const double2 *Gin, const double2 *min, double2 *cout)
+{
+    double2 A[S][S], m[S], c[S];
+#pragma unroll
+    for (int i = 0; i < S; ++i) {
+#pragma unroll
+        for (int j = 0; j < S; ++j) A[i][j] = Gin[i * S + j];
+        m[i] = min[i];
+    }
+#pragma unroll
+    for (int k = 0; k < S; ++k) {
+        int p = k;
+        double best = fabs(A[k][k].x) + fabs(A[k][k].y);
+#pragma unroll
+        for (int i = k + 1; i < S; ++i) {
+            const double v = fabs(A[i][k].x) + fabs(A[i][k].y);
+            if (v > best) {
+                best = v;
+                p = i;
+            }
+        }
+        if (best == 0.0) return false;
+#pragma unroll
+        for (int i = k + 1; i < S; ++i) {
+            const bool sw = p == i;
+#pragma unroll
+            for (int j = 0; j <= S; ++j) {       // column S: the right-hand side
+                double2 &a = j < S ? A[k][j < S ? j : 0] : m[k], &b = j < S ? A[i][j < S ? j : 0] : m[i];
+                const double2 t = a;
+                a = cmk<double>(sw ? b.x : t.x, sw ? b.y : t.y);
+                b = cmk<double>(sw ? t.x : b.x, sw ? t.y : b.y);
+            }
+        }
+#pragma unroll
+        for (int i = k + 1; i < S; ++i) {
+            const double2 l = cdiv<double>(A[i][k], A[k][k]);
+            A[i][k] = l;
+#pragma unroll
+            for (int j = k + 1; j < S; ++j) A[i][j] = csub<double>(A[i][j], cmul<double>(l, A[k][j]));
+        }
+    }
+#pragma unroll
+    for (int i = 0; i < S; ++i) {
+        double2 v = m[i];
+#pragma unroll
+        for (int j = 0; j < i; ++j) v = csub<double>(v, cmul<double>(A[i][j], c[j]));
+        c[i] = v;
+    }
+#pragma unroll
+    for (int i = S - 1; i >= 0; --i) {
+        double2 v = c[i];
+#pragma unroll
+        for (int j = i + 1; j < S; ++j) v = csub<double>(v, cmul<double>(A[i][j], c[j]));
+        c[i] = cdiv<double>(v, A[i][i]);
+    }
+#pragma unroll
+    for (int i = 0; i < S; ++i) cout[i] = c[i];
+    return true;
+}
+__device__ inline bool small_solve(const double2 *G, int s, const double2 *m, double2 *c)
+{
+    switch (s) {
+    case 1: return small_solve_reg<1>(G, m, c);
+    case 2: return small_solve_reg<2>(G, m, c);
+    case 3: return small_solve_reg<3>(G, m, c);
+    case 4: return small_solve_reg<4>(G, m, c);
+    default: return small_solve_lds(G, s, m, c);
+    }
+}
 
-__device__ void idr_finalize(const ProbDev *pd, SolveState *st, int kind, const double *v, int phase)
+// scalar state after a pass (one thread; st in LDS, v the pass's sums)
+__device__ inline void idr_advance(const ProbDev *pd, SolveState *st, int kind, const double *v)
 {
     const int s = st->s;
     if (kind == FIN_IDR_INIT) {
@@ -94,10 +158,8 @@ __device__ void idr_finalize(const ProbDev *pd, SolveState *st, int kind, const 
         st->best_mv = st->mv;
         return;
     }
-    if (phase != PH_RUN) return;
     const int mode = st->startup >= 0 ? 0 : (st->kstep == 0 ? 1 : 2);
     if (kind == FIN_IDR_OMEGA) {
-        if (mode == 2) return;
         st->mv += 1;
         double2 tv = cmk<double>(v[0], v[1]);
         double tt = v[2];
@@ -135,7 +197,44 @@ __device__ void idr_finalize(const ProbDev *pd, SolveState *st, int kind, const 
     if (!small_solve(st->G, s, st->m, st->c)) stop(st, RS_BREAK);
 }
 
+// Finaliser of the IDR passes: the state block is copied to LDS by all
+// threads, advanced there by one, and copied back (a chain of dependent
+// global accesses by one thread cost more than the sums).  Passes that reduce
+// nothing in the current mode (omega in steps k >= 1) return after the copy.
+__device__ void idr_finalize(const ProbDev *pd, int kind, bool gate)
+{
+    constexpr int SW = sizeof(SolveState) / 4, CW = sizeof(Ctrl) / 4;
+    static_assert(sizeof(SolveState) % 4 == 0 && sizeof(Ctrl) % 4 == 0 && SW <= HH_FIN_WG && CW <= HH_FIN_WG, "one word per thread");
+    __shared__ SolveState st;
+    __shared__ Ctrl ct;
+    __shared__ double res[4 * HH_MAX_S + 4];
+    const int t = threadIdx.x;
+    if (t < SW) ((uint32_t *)&st)[t] = ((const HH_GLOBAL uint32_t *)pd->st)[t];
+    __syncthreads();
+    if (kind != FIN_IDR_INIT && st.phase != PH_RUN) return;
+    const int mode = st.startup >= 0 ? 0 : (st.kstep == 0 ? 1 : 2);
+    if (kind == FIN_IDR_OMEGA) {
+        if (mode == 2) return;
+        reduce_partials(pd->part, pd->ngroup, 0, 3, res);
+    } else if (kind == FIN_IDR_STEP) {
+        reduce_partials(pd->part, pd->ngroup, 0, 1 + 2 * st.s, res);
+        if (mode == 0) reduce_partials(pd->part, pd->ngroup, 1 + 2 * HH_MAX_S, 2 * st.s, res + 1 + 2 * HH_MAX_S);
+    }
+    if (t == 0) {
+        idr_advance(pd, &st, kind, res);
+        mirror(ct, st);
+    }
+    __syncthreads();
+    if (t < SW) ((HH_GLOBAL uint32_t *)pd->st)[t] = ((const uint32_t *)&st)[t];
+    if (pd->ctrl && t < CW) ((HH_GLOBAL uint32_t *)pd->ctrl)[t] = ((const uint32_t *)&ct)[t];
+}
+
+// NS (4 or 8): the columns the passes are built for, at least every problem's
+// s.  With 8, IDR(4) held and reduced twice the values it has: the update
+// pass took 95 us at 128^3, 3.5 TB/s.
+
 // P1: v = r (start-up) or q = -sum_j dR_j c_j, v = r + q
+template <int NS>
 __global__ __launch_bounds__(HH_VWG) void k_idr_v(Ctx cx)
 {
     const Tile tl = tile_of(cx);
@@ -162,14 +261,14 @@ __global__ __launch_bounds__(HH_VWG) void k_idr_v(Ctx cx)
     for (int e = 0; e < HH_PER_SLOT; ++e) {
         const int64_t p = CHUNK_P(e);
         if (p < N) {
-            double2 col[HH_MAX_S];
+            double2 col[NS];
 #pragma unroll
-            for (int j = 0; j < HH_MAX_S; ++j)
+            for (int j = 0; j < NS; ++j)
                 if (j < ns) col[j] = ldg(dR, (int64_t)j * N + p);
             const double2 rv = ldg(r, p);
             double2 acc = cmul<double>(col[0], ct.c[0]);
 #pragma unroll
-            for (int j = 1; j < HH_MAX_S; ++j)
+            for (int j = 1; j < NS; ++j)
                 if (j < ns) acc = cadd<double>(acc, cmul<double>(col[j], ct.c[j]));
             const double2 qv = cmk<double>(-acc.x, -acc.y);
             stg(v, p, cadd<double>(rv, qv));
@@ -180,7 +279,7 @@ __global__ __launch_bounds__(HH_VWG) void k_idr_v(Ctx cx)
 
 // P3: t = H w with partials (t, v), (t, t)   (start-up, k = 0)
 //     dX_old = om w - sum_j dX_j c_j          (k >= 1)
-template <int DIM, typename SW>
+template <int DIM, typename SW, int NS>
 __global__ __launch_bounds__(HH_VWG) void k_idr_t(Ctx cx)
 {
     const Tile tl = tile_of(cx);
@@ -197,14 +296,14 @@ __global__ __launch_bounds__(HH_VWG) void k_idr_t(Ctx cx)
         for (int e = 0; e < HH_PER_SLOT; ++e) {
             const int64_t p = CHUNK_P(e);
             if (p < N) {
-                double2 col[HH_MAX_S];
+                double2 col[NS];
 #pragma unroll
-                for (int j = 0; j < HH_MAX_S; ++j)
+                for (int j = 0; j < NS; ++j)
                     if (j < ns) col[j] = ldg(dX, (int64_t)j * N + p);
                 const double2 wv = ld64(w, p);
                 double2 acc = cmul<double>(col[0], ct.c[0]);
 #pragma unroll
-                for (int j = 1; j < HH_MAX_S; ++j)
+                for (int j = 1; j < NS; ++j)
                     if (j < ns) acc = cadd<double>(acc, cmul<double>(col[j], ct.c[j]));
                 stg(dX, (int64_t)ct.old * N + p, csub<double>(cmul<double>(ct.om_idr, wv), acc));
             }
@@ -240,17 +339,17 @@ __global__ __launch_bounds__(HH_VWG) void k_idr_t(Ctx cx)
 }
 
 // P4: the dR/dX column of this step, r += dR, x += dX; partials ||r||^2,
-// P^H dR (and P^H r during start-up)
-template <int DIM, typename SW>
+// P^H dR (and P^H r during start-up).  All loads of a point are issued before
+// its first store.
+template <int DIM, typename SW, int NS>
 __global__ __launch_bounds__(HH_VWG) void k_idr_up(Ctx cx)
 {
-    constexpr int NV = 1 + 4 * HH_MAX_S;
     const Tile tl = tile_of(cx);
     const Ctrl ct = ctrl_of(cx, tl.prob);
     if (ct.phase != PH_RUN) return;
     const ProbDev *pd = cx.P + tl.prob;
     const HView h = hview(pd);
-    const int64_t N = h.N, base = (int64_t)tl.idx * HH_SPAN;
+    const int64_t N = h.N, p = (int64_t)tl.idx * HH_SPAN + threadIdx.x;
     const int ns = pd->nidr, mode = ct.mode;
     const double2 om = ct.om_idr;
     const SW *__restrict__ w = (const SW *)pd->vec[VS_W];
@@ -263,26 +362,31 @@ __global__ __launch_bounds__(HH_VWG) void k_idr_up(Ctx cx)
     const double2 *__restrict__ Pm = pd->P;
     double2 *__restrict__ dRo = dR + (int64_t)ct.old * N;
     double2 *__restrict__ dXo = dX + (int64_t)ct.old * N;
-    double acc[NV];
+    static_assert(HH_PER_SLOT == 1, "one unknown per thread");
+    double acc[1 + 2 * NS], acr[2 * NS];
 #pragma unroll
-    for (int k = 0; k < NV; ++k) acc[k] = 0.0;
-    for (int e = 0; e < HH_PER_SLOT; ++e) {
-        const int64_t p = CHUNK_P(e);
-        if (p >= N) continue;
-        double2 dr, dx;
+    for (int k = 0; k < 1 + 2 * NS; ++k) acc[k] = 0.0;
+#pragma unroll
+    for (int k = 0; k < 2 * NS; ++k) acr[k] = 0.0;
+    if (p < N) {
+        double2 dr, dx, pv[NS];
+#pragma unroll
+        for (int i = 0; i < NS; ++i)
+            if (i < ns) pv[i] = ldg(Pm, (int64_t)i * N + p);
+        const double2 r0 = ldg(r, p), x0 = ldg(x, p);
         if (mode == 0) {
             const double2 ot = cmul<double>(om, ldg(t, p));
             dx = cmul<double>(om, ld64(w, p));
             dr = cmk<double>(-ot.x, -ot.y);
         } else if (mode == 1) {
-            double2 col[HH_MAX_S];
+            double2 col[NS];
 #pragma unroll
-            for (int j = 0; j < HH_MAX_S; ++j)
+            for (int j = 0; j < NS; ++j)
                 if (j < ns) col[j] = ldg(dX, (int64_t)j * N + p);
             const double2 tv = ldg(t, p), qv = ldg(q, p), wv = ld64(w, p);
             double2 ax = cmul<double>(col[0], ct.c[0]);
 #pragma unroll
-            for (int j = 1; j < HH_MAX_S; ++j)
+            for (int j = 1; j < NS; ++j)
                 if (j < ns) ax = cadd<double>(ax, cmul<double>(col[j], ct.c[j]));
             dr = csub<double>(qv, cmul<double>(om, tv));
             dx = csub<double>(cmul<double>(om, wv), ax);
@@ -295,30 +399,26 @@ __global__ __launch_bounds__(HH_VWG) void k_idr_up(Ctx cx)
         }
         if (mode != 2) stg(dXo, p, dx);
         stg(dRo, p, dr);
-        const double2 rn = cadd<double>(ldg(r, p), dr);
+        const double2 rn = cadd<double>(r0, dr);
         stg(r, p, rn);
-        stg(x, p, cadd<double>(ldg(x, p), dx));
+        stg(x, p, cadd<double>(x0, dx));
         acc[0] = acc[0] + (rn.x * rn.x + rn.y * rn.y);
 #pragma unroll
-        for (int i = 0; i < HH_MAX_S; ++i) {
+        for (int i = 0; i < NS; ++i) {
             if (i < ns) {
-                const double2 pv = ldg(Pm, (int64_t)i * N + p);
-                acc[1 + 2 * i] = acc[1 + 2 * i] + (pv.x * dr.x + pv.y * dr.y);
-                acc[2 + 2 * i] = acc[2 + 2 * i] + (pv.x * dr.y - pv.y * dr.x);
+                acc[1 + 2 * i] = acc[1 + 2 * i] + (pv[i].x * dr.x + pv[i].y * dr.y);
+                acc[2 + 2 * i] = acc[2 + 2 * i] + (pv[i].x * dr.y - pv[i].y * dr.x);
                 if (mode == 0) {
-                    acc[1 + 2 * HH_MAX_S + 2 * i] = acc[1 + 2 * HH_MAX_S + 2 * i] + (pv.x * rn.x + pv.y * rn.y);
-                    acc[2 + 2 * HH_MAX_S + 2 * i] = acc[2 + 2 * HH_MAX_S + 2 * i] + (pv.x * rn.y - pv.y * rn.x);
+                    acr[2 * i] = acr[2 * i] + (pv[i].x * rn.x + pv[i].y * rn.y);
+                    acr[1 + 2 * i] = acr[1 + 2 * i] + (pv[i].x * rn.y - pv[i].y * rn.x);
                 }
             }
         }
     }
+    group_finish<1 + 2 * NS>(pd, tl.idx, acc);
     if (mode == 0) {
-        group_finish<NV>(pd, tl.idx, acc);
-    } else {
-        double a2[1 + 2 * HH_MAX_S];
-#pragma unroll
-        for (int k = 0; k < 1 + 2 * HH_MAX_S; ++k) a2[k] = acc[k];
-        group_finish<1 + 2 * HH_MAX_S>(pd, tl.idx, a2);
+        __syncthreads();
+        group_finish<2 * NS>(pd, tl.idx, acr, 1 + 2 * HH_MAX_S);
     }
 }
 

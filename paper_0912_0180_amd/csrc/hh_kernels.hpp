@@ -84,54 +84,6 @@ template <typename T> __device__ inline T wave_sum(T v)
     return (lane_value(v, 0) + lane_value(v, 16)) + (lane_value(v, 32) + lane_value(v, 48));
 }
 
-// Pairwise tree over the 256 thread slots of a 256-thread workgroup; thread 0
-// writes the NV sums to out[q * stride], q < NV.
-template <int NV>
-__device__ inline void block_reduce(double (&v)[NV], double *out, int64_t stride = 1)
-{
-    __shared__ double red[4 * NV];
-#pragma unroll
-    for (int q = 0; q < NV; ++q) v[q] = wave_sum(v[q]);
-    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-    if (lane == 0)
-#pragma unroll
-        for (int q = 0; q < NV; ++q) red[w * NV + q] = v[q];
-    __syncthreads();
-    if (threadIdx.x == 0)
-#pragma unroll
-        for (int q = 0; q < NV; ++q) out[q * stride] = (red[q] + red[NV + q]) + (red[2 * NV + q] + red[3 * NV + q]);
-}
-
-
-// Pairwise sum of v[0..n) (stride `stride`; LDS if LOCAL, else global) with
-// zero padding to a power of two >= 256, by one 256-thread workgroup; every
-// thread gets the sum.  Each thread sums its contiguous segment with the
-// iterative (binary counter) form of the pairwise tree, then the slots are
-// combined by block_reduce.
-template <bool LOCAL>
-__device__ inline double pairwise_wg(const double *v, int stride, int n)
-{
-    int np = 256;
-    while (np < n) np <<= 1;
-    const int seg = np >> 8;
-    const int beg = threadIdx.x * seg;
-    double stack[24];
-    int top = 0;
-    for (int i = 0; i < seg; ++i) {
-        int e = beg + i;
-        double x = e < n ? (LOCAL ? v[e * stride] : ldg(v, (int64_t)e * stride)) : 0.0;
-        for (int c = i; c & 1; c >>= 1) x = stack[--top] + x;
-        stack[top++] = x;
-    }
-    double r[1] = {stack[0]};
-    __shared__ double out[1];
-    block_reduce<1>(r, out);
-    __syncthreads();
-    double s = out[0];
-    __syncthreads();
-    return s;
-}
-
 // ---------------------------------------------------------------------------
 // descriptor views (copied to registers once per workgroup)
 // ---------------------------------------------------------------------------
@@ -349,7 +301,9 @@ __device__ inline void stencil_band(const HView &h, const S *__restrict__ x, con
 // finalisation: one workgroup per problem (k_fin) sums the chunk partials of
 // a reducing pass in the fixed pairwise order and advances the scalar state
 // ---------------------------------------------------------------------------
-#define HH_FIN_STAGE 16384
+#define HH_FIN_WG 1024            // threads of the finaliser
+#define HH_FIN_UNIT 128           // partials one wave sums in one load
+#define HH_FIN_SUMS 8192          // unit sums kept in LDS at a time
 
 __device__ inline bool cfin(double2 v) { return isfinite(v.x) && isfinite(v.y); }
 
@@ -365,159 +319,83 @@ __device__ inline void record(const ProbDev *pd, SolveState *st, double rel)
     if (pd->hist && st->mv - 1 < st->hist_len && st->mv >= 1) pd->hist[st->mv - 1] = rel;
 }
 
-// Sums value first + q (q < nv) of the chunk partials, stored value-major
-// (part[v * n + c] for chunk c of n), each by the pairwise tree over the
-// zero-padded power-of-two length; results in out[q].  The partials are
-// staged in LDS in blocks of HH_FIN_STAGE entries (an aligned power-of-two
-// block of a pairwise tree is itself a subtree, so block sums combine
-// exactly).
-// np = PER * 256 partials of each of G values.  Thread t loads the aligned
-// block [t PER, (t+1) PER) of each value (consecutive addresses, zero past
-// n) and sums it pairwise in registers; the 256 block sums are combined by
-// the wave butterfly and the four-wave sum (block_reduce), which is the same
-// tree.  Loading the block directly, rather than coalesced and transposed
-// through LDS, saves two barriers per value.
-template <int PER, int G>
-__device__ inline void reduce_values_blocked(const double *part, int n, int64_t off, int ng, double *out)
-{
-    const int t = (int)threadIdx.x;
-    double r[G][PER];
-#pragma unroll
-    for (int g = 0; g < G; ++g)
-#pragma unroll
-        for (int i = 0; i < PER; ++i) {
-            const int e = t * PER + i;
-            r[g][i] = (g < ng && e < n) ? ldg(part, off + (int64_t)g * n + e) : 0.0;
-        }
-    double sums[G];
-#pragma unroll
-    for (int g = 0; g < G; ++g) {
-#pragma unroll
-        for (int w = 1; w < PER; w <<= 1)
-#pragma unroll
-            for (int i = 0; i + w < PER; i += 2 * w) r[g][i] = r[g][i] + r[g][i + w];
-        sums[g] = r[g][0];
-    }
-    __shared__ double tmp[G];
-    block_reduce<G>(sums, tmp);
-    __syncthreads();
-    if (t < ng) out[t] = tmp[t];
-}
+typedef double hh_dvec2u __attribute__((ext_vector_type(2), aligned(8)));
 
-__device__ void reduce_partials(const double *part, int n, int first, int nv, double *out)
+// Sums value first + q (q < nv) of the group partials, stored value-major
+// (part[v * n + c] for group c of n), each by the pairwise tree over the
+// zero-padded power-of-two length; results in out[q] (LDS), visible to every
+// thread.  A wave takes units of 128 consecutive partials: one 16-byte load
+// per lane (a value's partials start 8-byte aligned), the pair in the lane,
+// then the tree over the lanes (wave_sum).  An aligned power-of-two block of a
+// pairwise tree is itself a subtree, so the unit sums, kept in LDS, combine by
+// the rest of it, one wave per value.  Loads are whole lines: with a thread
+// loading its own block of up to 32 partials every load touched 64 lines, and
+// 9 values of 4096 partials took 30 us (now 2).
+__device__ inline void reduce_partials(const double *part, int n, int first, int nv, double *out)
 {
-    __shared__ double stage[HH_FIN_STAGE];
-    __shared__ double bsum[4 * HH_MAX_S + 4][64];
-    int np = 1;
-    while (np < n) np <<= 1;
-    if (np >= HH_WG && np <= 32 * HH_WG) {
-        // groups of up to 4 values in flight (1 for the longest blocks); the
-        // transpose uses the staging buffer
-        const int per = np / HH_WG, G = per <= 16 ? 4 : 1;
-        for (int q = 0; q < nv; q += G) {
-            const int64_t off = (int64_t)(first + q) * n;
-            const int ng = nv - q < G ? nv - q : G;
-            switch (per) {
-            case 1: reduce_values_blocked<1, 4>(part, n, off, ng, out + q); break;
-            case 2: reduce_values_blocked<2, 4>(part, n, off, ng, out + q); break;
-            case 4: reduce_values_blocked<4, 4>(part, n, off, ng, out + q); break;
-            case 8: reduce_values_blocked<8, 4>(part, n, off, ng, out + q); break;
-            case 16: reduce_values_blocked<16, 4>(part, n, off, ng, out + q); break;
-            default: reduce_values_blocked<32, 1>(part, n, off, ng, out + q); break;
+    __shared__ double sums[HH_FIN_SUMS];
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6), nw = HH_FIN_WG / 64;
+    const int U = (n + HH_FIN_UNIT - 1) / HH_FIN_UNIT;
+    int per = 1;                       // unit sums per lane of the second step
+    while (64 * per < U) per <<= 1;
+    const int qstep = HH_FIN_SUMS / (64 * per);
+    const float ru = 1.0f / (float)U;  // g / U: exact, a quotient is at most 33 and 0.5 / U from the next
+    auto value_of = [&](int g) { return __builtin_amdgcn_readfirstlane((int)(((float)g + 0.5f) * ru)); };
+    for (int q0 = 0; q0 < nv; q0 += qstep) {
+        const int nq = min(nv - q0, qstep), T = nq * U;
+        constexpr int B = 8;           // units in flight per wave
+        for (int g0 = wave; g0 < T; g0 += B * nw) {
+            double2 v[B];
+#pragma unroll
+            for (int b = 0; b < B; ++b) {
+                const int g = g0 + b * nw, q = value_of(g), e = (g - q * U) * HH_FIN_UNIT + 2 * lane;
+                const double *p = part + (int64_t)(first + q0 + q) * n;
+                v[b] = cmk<double>(0.0, 0.0);
+                if (g < T && e + 1 < n) {
+                    const hh_dvec2u w = *(const HH_GLOBAL hh_dvec2u *)(p + e);
+                    v[b] = cmk<double>(w.x, w.y);
+                } else if (g < T && e < n) {
+                    v[b].x = ldg(p, e);
+                }
             }
-            __syncthreads();   // block_reduce's LDS is reused by the next group
-        }
-        return;
-    }
-    if (np > 32 * HH_WG && np <= 64 * 32 * HH_WG) {
-        // longer: aligned blocks of 32 * 256 partials (subtrees) by the
-        // blocked path one value at a time, then the block sums pairwise
-        constexpr int B = 32 * HH_WG;
-        const int nblk = np / B;
-        for (int q = 0; q < nv; ++q) {
-            for (int b = 0; b < nblk; ++b) {
-                const int valid = n - b * B < B ? (n - b * B > 0 ? n - b * B : 0) : B;
-                reduce_values_blocked<32, 1>(part, valid, (int64_t)(first + q) * n + (int64_t)b * B, 1, &bsum[q][b]);
-                __syncthreads();
+#pragma unroll
+            for (int b = 0; b < B; ++b) {
+                const int g = g0 + b * nw, q = value_of(g);
+                if (g >= T) break;
+                const double r = wave_sum(v[b].x + v[b].y);
+                if (lane == 0) sums[q * 64 * per + (g - q * U)] = r;
             }
-        }
-        if (threadIdx.x < nv) {
-            const int q = threadIdx.x;
-            for (int w = 1; w < nblk; w <<= 1)
-                for (int i = 0; i + w < nblk; i += 2 * w) bsum[q][i] = bsum[q][i] + bsum[q][i + w];
-            out[q] = bsum[q][0];
         }
         __syncthreads();
-        return;
-    }
-    // values per staging pass: all nv at once when they fit
-    const int blk = np < HH_FIN_STAGE ? np : HH_FIN_STAGE;
-    const int qstep = (HH_FIN_STAGE / blk) < nv ? (HH_FIN_STAGE / blk) : nv;
-    const int nblk = np / blk;
-    for (int q0 = 0; q0 < nv; q0 += qstep) {
-        const int nq = nv - q0 < qstep ? nv - q0 : qstep;
-        for (int b = 0; b < nblk; ++b) {
-            const int tot = nq * blk;
-            for (int e0 = 0; e0 < tot; e0 += 16 * HH_WG) {
-                double tmp[16];
-#pragma unroll
-                for (int u = 0; u < 16; ++u) {
-                    const int e = e0 + threadIdx.x + u * HH_WG;
-                    tmp[u] = 0.0;
-                    if (e < tot) {
-                        const int qq = e / blk, c = b * blk + (e - qq * blk);
-                        if (c < n) tmp[u] = ldg(part, (int64_t)(first + q0 + qq) * n + c);
-                    }
-                }
-#pragma unroll
-                for (int u = 0; u < 16; ++u) {
-                    const int e = e0 + threadIdx.x + u * HH_WG;
-                    if (e < tot) stage[e] = tmp[u];
-                }
-            }
-            __syncthreads();
-            for (int w = 1; w < blk; w <<= 1) {
-                const int pairs = blk / (2 * w);
-                for (int e = threadIdx.x; e < nq * pairs; e += HH_WG) {
-                    const int qq = e / pairs, i = (e - qq * pairs) * 2 * w;
-                    stage[qq * blk + i] = stage[qq * blk + i] + stage[qq * blk + i + w];
-                }
-                __syncthreads();
-            }
-            if (threadIdx.x < nq) bsum[q0 + threadIdx.x][b] = stage[threadIdx.x * blk];
-            __syncthreads();
+        for (int q = wave; q < nq; q += nw) {
+            double *u = sums + q * 64 * per + lane * per;
+            for (int i = 0; i < per; ++i)
+                if (lane * per + i >= U) u[i] = 0.0;
+            for (int w = 1; w < per; w <<= 1)
+                for (int i = 0; i + w < per; i += 2 * w) u[i] = u[i] + u[i + w];
+            const double r = wave_sum(u[0]);
+            if (lane == 0) out[q0 + q] = r;
         }
+        __syncthreads();
     }
-    // combine block sums (nblk is a power of two, at most 64 here)
-    if (threadIdx.x < nv) {
-        const int q = threadIdx.x;
-        for (int w = 1; w < nblk; w <<= 1)
-            for (int i = 0; i + w < nblk; i += 2 * w) bsum[q][i] = bsum[q][i] + bsum[q][i + w];
-        out[q] = bsum[q][0];
-    }
-    __syncthreads();
 }
 
-// copy of the phase and scalars into the plan's control block
-__device__ inline void mirror(const ProbDev *pd, const SolveState *st)
+// the control block of an IDR state
+__device__ inline void mirror(Ctrl &c, const SolveState &st)
 {
-    if (!pd->ctrl) return;
-    Ctrl c;
-    c.phase = st->phase;
-    c.mode = st->startup >= 0 ? 0 : (st->kstep == 0 ? 1 : 2);
-    c.old = st->startup >= 0 ? st->startup : st->oldest;
-    c.reason = st->reason;
-    c.alpha = st->alpha;
-    c.beta = st->beta;
-    c.omega = st->omega;
-    c.om_idr = st->om_idr;
-    for (int i = 0; i < 8; ++i) c.c[i] = i < HH_MAX_S ? st->c[i] : cmk<double>(0.0, 0.0);
-    *pd->ctrl = c;
+    c.phase = st.phase;
+    c.mode = st.startup >= 0 ? 0 : (st.kstep == 0 ? 1 : 2);
+    c.old = st.startup >= 0 ? st.startup : st.oldest;
+    c.reason = st.reason;
+    c.alpha = st.alpha;
+    c.beta = st.beta;
+    c.omega = st.omega;
+    c.om_idr = st.om_idr;
+    for (int i = 0; i < 8; ++i) c.c[i] = i < HH_MAX_S ? st.c[i] : cmk<double>(0.0, 0.0);
 }
 
 // defined with the IDR kernels
-__device__ void idr_finalize(const ProbDev *pd, SolveState *st, int kind, const double *s, int phase);
-__device__ int idr_nvals(const ProbDev *pd, int kind);
+__device__ void idr_finalize(const ProbDev *pd, int kind, bool gate);
 
 // Scalar state of a Bi-CGSTAB solve, copied to registers before the
 // reduction (its loads overlap the partial sums) and written back once.
@@ -564,6 +442,10 @@ __device__ inline bool fin_runs(int kind, int phase)
 // decided after the state and the partials are loaded
 __device__ __forceinline__ void finalize(const ProbDev *pd, int kind, bool gate)
 {
+    if (kind >= FIN_IDR_OMEGA) {
+        idr_finalize(pd, kind, gate);
+        return;
+    }
     SolveState *st = pd->st;
     BiLoc b;
     b.phase = st->phase;
@@ -586,19 +468,13 @@ __device__ __forceinline__ void finalize(const ProbDev *pd, int kind, bool gate)
     b.drift_stall = st->drift_stall;
     b.drift_grow = st->drift_grow;
     const int phase = b.phase;
-    const int nv = kind >= FIN_IDR_OMEGA ? idr_nvals(pd, kind)
-                 : (kind == FIN_BNORM || kind == FIN_TRUE) ? 1 : (kind == FIN_ALPHA ? 2 : (kind == FIN_OMEGA ? 4 : 3));
+    const int nv = (kind == FIN_BNORM || kind == FIN_TRUE) ? 1 : (kind == FIN_ALPHA ? 2 : (kind == FIN_OMEGA ? 4 : 3));
     const int first = (kind == FIN_BNORM || kind == FIN_TRUE) ? 2 : 0;
-    __shared__ double res[4 * HH_MAX_S + 4];
+    __shared__ double res[4];
     reduce_partials(pd->part, pd->ngroup, first, nv, res);
     const double *s = res;
     if (threadIdx.x != 0) return;
     if (gate && !fin_runs(kind, phase)) return;
-    if (kind >= FIN_IDR_OMEGA) {
-        idr_finalize(pd, st, kind, s, phase);
-        mirror(pd, st);
-        return;
-    }
     switch (kind) {
     case FIN_BNORM:
         b.bnorm = sqrt(s[0]);
@@ -739,7 +615,7 @@ __device__ inline void group_finish(const ProbDev *pd, int grp, double (&acc)[NV
 
 // One workgroup per problem: sums the chunk partials of the pass just run and
 // advances the scalar state (kind = FinKind).
-__global__ __launch_bounds__(HH_WG) void k_fin(Ctx cx, const int *__restrict__ probs, int kind)
+__global__ __launch_bounds__(HH_FIN_WG) void k_fin(Ctx cx, const int *__restrict__ probs, int kind)
 {
     const int prob = probs ? probs[blockIdx.x] : 0;
     const ProbDev *pd = cx.P + prob;
@@ -754,7 +630,7 @@ __global__ __launch_bounds__(HH_WG) void k_fin(Ctx cx, const int *__restrict__ p
 // dependent round trips to memory the other XCDs wrote); the phase gate is
 // applied after them, on the state block's phase (which the control block
 // mirrors).
-__global__ __launch_bounds__(HH_WG) void k_fin1(int kind, ProbDev pv)
+__global__ __launch_bounds__(HH_FIN_WG) void k_fin1(int kind, ProbDev pv)
 {
     finalize(&pv, kind, true);
 }

@@ -1234,11 +1234,11 @@ void launch_vcycle(const Plan &pl, int fsel, int osel, const void *fptr, void *o
 void launch_fin(const Plan &pl, const int *probs, int n, int kind, hipStream_t s)
 {
     if (pl.count == 1 && !pl.host.empty()) {
-        if (n > 0) hipLaunchKernelGGL(k_fin1, dim3(1), dim3(HH_WG), 0, s, kind, pl.host[0]);
+        if (n > 0) hipLaunchKernelGGL(k_fin1, dim3(1), dim3(HH_FIN_WG), 0, s, kind, pl.host[0]);
         return;
     }
     const Ctx c = ctx_of(pl, pl.chunks);
-    LAUNCH(k_fin, n, s, c, pl.count == 1 ? nullptr : probs, kind);
+    if (n > 0) hipLaunchKernelGGL(k_fin, dim3(n), dim3(HH_FIN_WG), 0, s, c, pl.count == 1 ? nullptr : probs, kind);
 }
 
 template <int DIM, typename SP>
@@ -1270,27 +1270,34 @@ void launch_bicg_iteration(const Plan &pl, hipStream_t s)
     }
 }
 
-template <int DIM, typename SW>
+template <int DIM, typename SW, int NS>
 static void idr_step_t(const Plan &pl, hipStream_t s)
 {
     const Ctx c = ctx_of(pl, pl.chunks);
     const int n = pl.chunks.n;
-    LAUNCH_K(k_idr_v, n, s, c);
+    LAUNCH_K(k_idr_v<NS>, n, s, c);
     launch_vcycle(pl, VS_V, VS_W, nullptr, nullptr, s);
-    LAUNCH_K((k_idr_t<DIM, SW>), n, s, c);
+    LAUNCH_K((k_idr_t<DIM, SW, NS>), n, s, c);
     launch_fin(pl, pl.fin, pl.nfin, FIN_IDR_OMEGA, s);
-    LAUNCH_K((k_idr_up<DIM, SW>), n, s, c);
+    LAUNCH_K((k_idr_up<DIM, SW, NS>), n, s, c);
     launch_fin(pl, pl.fin, pl.nfin, FIN_IDR_STEP, s);
+}
+template <int DIM, typename SW> static void idr_step_s(const Plan &pl, hipStream_t s)
+{
+    int ms = 0;
+    for (const ProbDev &p : pl.host) ms = std::max(ms, p.nidr);
+    if (ms <= 4) idr_step_t<DIM, SW, 4>(pl, s);
+    else idr_step_t<DIM, SW, HH_MAX_S>(pl, s);
 }
 
 void launch_idr_step(const Plan &pl, hipStream_t s)
 {
     if (pl.dim == 2) {
-        if (pl.fp32) idr_step_t<2, float2>(pl, s);
-        else idr_step_t<2, double2>(pl, s);
+        if (pl.fp32) idr_step_s<2, float2>(pl, s);
+        else idr_step_s<2, double2>(pl, s);
     } else {
-        if (pl.fp32) idr_step_t<3, float2>(pl, s);
-        else idr_step_t<3, double2>(pl, s);
+        if (pl.fp32) idr_step_s<3, float2>(pl, s);
+        else idr_step_s<3, double2>(pl, s);
     }
 }
 
