@@ -23,185 +23,64 @@
 
 namespace hh {
 
-// s x s complex LU solve G c = m (G row major), same algorithm as the host
-// setup's dense LU.  Returns false for an exactly singular pivot.  One thread,
-// in LDS; for s <= 4 in registers (S = s, rows swapped by selects), where it
-// takes about 2 us instead of waiting for LDS between dependent steps.
-__device__ inline bool small_solve_lds(const double2 *Gin, int s, const double2 *m, double2 *c)
+// s x s complex LU solve G c = m (G row major, in LDS), same algorithm and
+// order per value as the host setup's dense LU, by one wave: lane 8 i + j holds
+// entry (i, j) and, in every lane of a row, that row's right-hand side.  The
+// pivot, row and column values come from their lanes, a lane known to the whole
+// wave by v_readlane.  Returns false for an exactly singular pivot.  c: LDS.
+__device__ inline double2 lane_get(double2 v, int l) { return cmk<double>(__shfl(v.x, l), __shfl(v.y, l)); }
+__device__ inline double2 lane_one(double2 v, int l) { return cmk<double>(lane_value(v.x, l), lane_value(v.y, l)); }   // l uniform
+__device__ __forceinline__ bool small_solve(const double2 *G, int s, const double2 *m, double2 *c)
 {
-    __shared__ double2 A[HH_MAX_S * HH_MAX_S];   // thread 0 only (keeps the solve out of scratch memory)
-    __shared__ int perm[HH_MAX_S];
-    for (int i = 0; i < s * s; ++i) A[i] = Gin[i];
-    for (int i = 0; i < s; ++i) perm[i] = i;
+    const int lane = threadIdx.x & 63, i = lane >> 3, j = lane & 7;
+    const bool in = i < s && j < s;
+    double2 a = in ? G[i * s + j] : cmk<double>(0.0, 0.0);
+    double2 v = i < s ? m[i] : cmk<double>(0.0, 0.0);
     for (int k = 0; k < s; ++k) {
+        // first maximum of |re| + |im| in column k from row k
+        const double ab = fabs(a.x) + fabs(a.y);
         int p = k;
-        double best = fabs(A[k * s + k].x) + fabs(A[k * s + k].y);
-        for (int i = k + 1; i < s; ++i) {
-            double v = fabs(A[i * s + k].x) + fabs(A[i * s + k].y);
-            if (v > best) {
-                best = v;
-                p = i;
+        double best = lane_value(ab, 9 * k);
+        for (int r = k + 1; r < s; ++r) {
+            const double w = lane_value(ab, 8 * r + k);
+            if (w > best) {
+                best = w;
+                p = r;
             }
         }
-        if (best == 0.0) return false;
+        if (best == 0.0) return false;   // uniform over the wave, as p
+        p = __builtin_amdgcn_readfirstlane(p);
         if (p != k) {
-            for (int j = 0; j < s; ++j) {
-                double2 t = A[k * s + j];
-                A[k * s + j] = A[p * s + j];
-                A[p * s + j] = t;
-            }
-            int t = perm[k];
-            perm[k] = perm[p];
-            perm[p] = t;
+            const int from = i == k ? p : i == p ? k : i;
+            a = lane_get(a, 8 * from + j);
+            v = lane_get(v, 8 * from);
         }
-        const double2 piv = A[k * s + k];
-        for (int i = k + 1; i < s; ++i) {
-            double2 l = cdiv<double>(A[i * s + k], piv);
-            A[i * s + k] = l;
-            for (int j = k + 1; j < s; ++j) A[i * s + j] = csub<double>(A[i * s + j], cmul<double>(l, A[k * s + j]));
-        }
+        const double2 l = cdiv<double>(lane_get(a, 8 * i + k), lane_one(a, 9 * k));
+        const double2 u = lane_get(a, 8 * k + j);
+        if (i > k) a = j == k ? l : j > k ? csub<double>(a, cmul<double>(l, u)) : a;
     }
-    for (int i = 0; i < s; ++i) {
-        double2 v = m[perm[i]];
-        for (int j = 0; j < i; ++j) v = csub<double>(v, cmul<double>(A[i * s + j], c[j]));
-        c[i] = v;
+    // forward: row i takes the terms of columns 0 .. i - 1 in order
+    for (int k = 0; k + 1 < s; ++k) {
+        const double2 ck = lane_one(v, 8 * k), l = lane_get(a, 8 * i + k);
+        if (i > k) v = csub<double>(v, cmul<double>(l, ck));
     }
-    for (int i = s - 1; i >= 0; --i) {
-        double2 v = c[i];
-        for (int j = i + 1; j < s; ++j) v = csub<double>(v, cmul<double>(A[i * s + j], c[j]));
-        c[i] = cdiv<double>(v, A[i * s + i]);
+    // backward: row r, columns r + 1 .. s - 1 in order, each c in its row's lanes
+    for (int r = s - 1; r >= 0; --r) {
+        double2 w = lane_one(v, 8 * r);
+        for (int k = r + 1; k < s; ++k) w = csub<double>(w, cmul<double>(lane_one(a, 8 * r + k), lane_one(v, 8 * k)));
+        w = cdiv<double>(w, lane_one(a, 9 * r));
+        if (i == r) v = w;
     }
+    if (j == 0 && i < s) c[i] = v;
     return true;
 }
-template <int S> __device__ inline bool small_solve_reg(const double2 *Gin, const double2 *min, double2 *cout)
-{
-    double2 A[S][S], m[S], c[S];
-#pragma unroll
-    for (int i = 0; i < S; ++i) {
-#pragma unroll
-        for (int j = 0; j < S; ++j) A[i][j] = Gin[i * S + j];
-        m[i] = min[i];
-    }
-#pragma unroll
-    for (int k = 0; k < S; ++k) {
-        int p = k;
-        double best = fabs(A[k][k].x) + fabs(A[k][k].y);
-#pragma unroll
-        for (int i = k + 1; i < S; ++i) {
-            const double v = fabs(A[i][k].x) + fabs(A[i][k].y);
-            if (v > best) {
-                best = v;
-                p = i;
-            }
-        }
-        if (best == 0.0) return false;
-#pragma unroll
-        for (int i = k + 1; i < S; ++i) {
-            const bool sw = p == i;
-#pragma unroll
-            for (int j = 0; j <= S; ++j) {       // column S: the right-hand side
-                double2 &a = j < S ? A[k][j < S ? j : 0] : m[k], &b = j < S ? A[i][j < S ? j : 0] : m[i];
-                const double2 t = a;
-                a = cmk<double>(sw ? b.x : t.x, sw ? b.y : t.y);
-                b = cmk<double>(sw ? t.x : b.x, sw ? t.y : b.y);
-            }
-        }
-#pragma unroll
-        for (int i = k + 1; i < S; ++i) {
-            const double2 l = cdiv<double>(A[i][k], A[k][k]);
-            A[i][k] = l;
-#pragma unroll
-            for (int j = k + 1; j < S; ++j) A[i][j] = csub<double>(A[i][j], cmul<double>(l, A[k][j]));
-        }
-    }
-#pragma unroll
-    for (int i = 0; i < S; ++i) {
-        double2 v = m[i];
-#pragma unroll
-        for (int j = 0; j < i; ++j) v = csub<double>(v, cmul<double>(A[i][j], c[j]));
-        c[i] = v;
-    }
-#pragma unroll
-    for (int i = S - 1; i >= 0; --i) {
-        double2 v = c[i];
-#pragma unroll
-        for (int j = i + 1; j < S; ++j) v = csub<double>(v, cmul<double>(A[i][j], c[j]));
-        c[i] = cdiv<double>(v, A[i][i]);
-    }
-#pragma unroll
-    for (int i = 0; i < S; ++i) cout[i] = c[i];
-    return true;
-}
-__device__ inline bool small_solve(const double2 *G, int s, const double2 *m, double2 *c)
-{
-    switch (s) {
-    case 1: return small_solve_reg<1>(G, m, c);
-    case 2: return small_solve_reg<2>(G, m, c);
-    case 3: return small_solve_reg<3>(G, m, c);
-    case 4: return small_solve_reg<4>(G, m, c);
-    default: return small_solve_lds(G, s, m, c);
-    }
-}
 
-// scalar state after a pass (one thread; st in LDS, v the pass's sums)
-__device__ inline void idr_advance(const ProbDev *pd, SolveState *st, int kind, const double *v)
-{
-    const int s = st->s;
-    if (kind == FIN_IDR_INIT) {
-        st->phase = PH_RUN;
-        st->reason = RS_NONE;
-        st->startup = 0;
-        st->kstep = 0;
-        st->oldest = 0;
-        st->om_idr = cmk<double>(1.0, 0.0);
-        st->best_rel = INFINITY;
-        st->best_mv = st->mv;
-        return;
-    }
-    const int mode = st->startup >= 0 ? 0 : (st->kstep == 0 ? 1 : 2);
-    if (kind == FIN_IDR_OMEGA) {
-        st->mv += 1;
-        double2 tv = cmk<double>(v[0], v[1]);
-        double tt = v[2];
-        if (!cfin(tv) || !isfinite(tt)) { stop(st, RS_NONFIN); return; }
-        if (tt == 0.0) { stop(st, RS_BREAK); return; }
-        st->om_idr = cmk<double>(tv.x / tt, tv.y / tt);
-        return;
-    }
-    // FIN_IDR_STEP
-    if (mode == 2) st->mv += 1;
-    if (mode != 0) st->it += 1;
-    const double rel = sqrt(v[0]) / st->bnorm;
-    record(pd, st, rel);
-    if (!isfinite(rel)) { stop(st, RS_NONFIN); return; }
-    if (rel < st->tol) { stop(st, RS_CONV); return; }
-    if (st->mv >= st->max_mv) { stop(st, RS_MAXMV); return; }
-    if (st->guard && drift(rel, st->mv, st->best_rel, st->best_mv, st->drift_grow, st->drift_stall)) { stop(st, RS_DRIFT); return; }
-    const int col = mode == 0 ? st->startup : st->oldest;
-    for (int i = 0; i < s; ++i) {
-        double2 dm = cmk<double>(v[1 + 2 * i], v[2 + 2 * i]);
-        st->G[i * s + col] = dm;
-        if (mode != 0) st->m[i] = cadd<double>(st->m[i], dm);
-    }
-    if (mode == 0) {
-        st->startup += 1;
-        if (st->startup < s) return;
-        st->startup = -1;
-        st->oldest = 0;
-        st->kstep = 0;
-        for (int i = 0; i < s; ++i) st->m[i] = cmk<double>(v[1 + 2 * HH_MAX_S + 2 * i], v[2 + 2 * HH_MAX_S + 2 * i]);
-    } else {
-        st->oldest = st->oldest + 1 == s ? 0 : st->oldest + 1;
-        st->kstep = st->kstep + 1 == s + 1 ? 0 : st->kstep + 1;
-    }
-    if (!small_solve(st->G, s, st->m, st->c)) stop(st, RS_BREAK);
-}
-
-// Finaliser of the IDR passes: the state block is copied to LDS by all
-// threads, advanced there by one, and copied back (a chain of dependent
-// global accesses by one thread cost more than the sums).  Passes that reduce
-// nothing in the current mode (omega in steps k >= 1) return after the copy.
-__device__ void idr_finalize(const ProbDev *pd, int kind, bool gate)
+// Finaliser of the IDR passes.  The state block is copied to LDS by all
+// threads, advanced there by the first wave (every lane the same scalars, row i
+// of G and m in lane i) and copied back: a chain of dependent global accesses
+// by one thread cost more than the sums.  Passes that reduce nothing in the
+// current mode (omega in steps k >= 1) return after the copy.
+__device__ __forceinline__ void idr_finalize(const ProbDev *pd, int kind, bool gate, int ng)
 {
     constexpr int SW = sizeof(SolveState) / 4, CW = sizeof(Ctrl) / 4;
     static_assert(sizeof(SolveState) % 4 == 0 && sizeof(Ctrl) % 4 == 0 && SW <= HH_FIN_WG && CW <= HH_FIN_WG, "one word per thread");
@@ -211,18 +90,90 @@ __device__ void idr_finalize(const ProbDev *pd, int kind, bool gate)
     const int t = threadIdx.x;
     if (t < SW) ((uint32_t *)&st)[t] = ((const HH_GLOBAL uint32_t *)pd->st)[t];
     __syncthreads();
-    if (kind != FIN_IDR_INIT && st.phase != PH_RUN) return;
-    const int mode = st.startup >= 0 ? 0 : (st.kstep == 0 ? 1 : 2);
+    const int s = st.s, max_mv = st.max_mv, hist_len = st.hist_len, guard = st.guard, stall = st.drift_stall;
+    const double tol = st.tol, bnorm = st.bnorm, grow = st.drift_grow;
+    double rel = st.rel, best_rel = st.best_rel;
+    int phase = st.phase, reason = st.reason, mv = st.mv, it = st.it, best_mv = st.best_mv, startup = st.startup, kstep = st.kstep,
+        oldest = st.oldest;
+    double2 om = st.om_idr;
+    if (kind != FIN_IDR_INIT && phase != PH_RUN) return;
+    const int mode = startup >= 0 ? 0 : (kstep == 0 ? 1 : 2);
     if (kind == FIN_IDR_OMEGA) {
         if (mode == 2) return;
-        reduce_partials(pd->part, pd->ngroup, 0, 3, res);
+        reduce_partials<HH_FIN_WG / 64>(pd->part, pd->ngroup, ng, 0, 3, res);
     } else if (kind == FIN_IDR_STEP) {
-        reduce_partials(pd->part, pd->ngroup, 0, 1 + 2 * st.s, res);
-        if (mode == 0) reduce_partials(pd->part, pd->ngroup, 1 + 2 * HH_MAX_S, 2 * st.s, res + 1 + 2 * HH_MAX_S);
+        reduce_partials<HH_FIN_WG / 64>(pd->part, pd->ngroup, ng, 0, 1 + 2 * s, res);
+        if (mode == 0) reduce_partials<HH_FIN_WG / 64>(pd->part, pd->ngroup, ng, 1 + 2 * HH_MAX_S, 2 * s, res + 1 + 2 * HH_MAX_S);
     }
-    if (t == 0) {
-        idr_advance(pd, &st, kind, res);
-        mirror(ct, st);
+    if (t < 64) {
+        auto halt = [&](int why) {
+            phase = PH_STOP;
+            reason = why;
+        };
+        auto step = [&]() {
+            if (kind == FIN_IDR_INIT) {
+                phase = PH_RUN;
+                reason = RS_NONE;
+                startup = kstep = oldest = 0;
+                om = cmk<double>(1.0, 0.0);
+                best_rel = INFINITY;
+                best_mv = mv;
+                return;
+            }
+            if (kind == FIN_IDR_OMEGA) {
+                mv += 1;
+                const double2 tv = cmk<double>(res[0], res[1]);
+                const double tt = res[2];
+                if (!cfin(tv) || !isfinite(tt)) return halt(RS_NONFIN);
+                if (tt == 0.0) return halt(RS_BREAK);
+                om = cmk<double>(tv.x / tt, tv.y / tt);
+                return;
+            }
+            // FIN_IDR_STEP
+            if (mode == 2) mv += 1;
+            if (mode != 0) it += 1;
+            rel = sqrt(res[0]) / bnorm;
+            if (t == 0 && pd->hist && mv - 1 < hist_len && mv >= 1) pd->hist[mv - 1] = rel;
+            if (!isfinite(rel)) return halt(RS_NONFIN);
+            if (rel < tol) return halt(RS_CONV);
+            if (mv >= max_mv) return halt(RS_MAXMV);
+            if (guard && drift(rel, mv, best_rel, best_mv, grow, stall)) return halt(RS_DRIFT);
+            const int col = mode == 0 ? startup : oldest;
+            const bool last = mode == 0 && startup + 1 == s;     // the start-up's m = P^H r
+            if (t < s) {
+                const double2 dm = cmk<double>(res[1 + 2 * t], res[2 + 2 * t]);
+                st.G[t * s + col] = dm;
+                if (mode != 0) st.m[t] = cadd<double>(st.m[t], dm);
+                else if (last) st.m[t] = cmk<double>(res[1 + 2 * HH_MAX_S + 2 * t], res[2 + 2 * HH_MAX_S + 2 * t]);
+            }
+            if (mode == 0) {
+                startup += 1;
+                if (!last) return;
+                startup = -1;
+                oldest = kstep = 0;
+            } else {
+                oldest = oldest + 1 == s ? 0 : oldest + 1;
+                kstep = kstep + 1 == s + 1 ? 0 : kstep + 1;
+            }
+            __builtin_amdgcn_wave_barrier();
+            if (!small_solve(st.G, s, st.m, st.c)) halt(RS_BREAK);
+        };
+        step();
+        __builtin_amdgcn_wave_barrier();
+        if (t == 0) {
+            st.phase = phase;
+            st.reason = reason;
+            st.mv = mv;
+            st.it = it;
+            st.rel = rel;
+            st.best_rel = best_rel;
+            st.best_mv = best_mv;
+            st.startup = startup;
+            st.kstep = kstep;
+            st.oldest = oldest;
+            st.om_idr = om;
+            mirror(ct, st);
+        }
     }
     __syncthreads();
     if (t < SW) ((HH_GLOBAL uint32_t *)pd->st)[t] = ((const uint32_t *)&st)[t];
@@ -363,11 +314,9 @@ __global__ __launch_bounds__(HH_VWG) void k_idr_up(Ctx cx)
     double2 *__restrict__ dRo = dR + (int64_t)ct.old * N;
     double2 *__restrict__ dXo = dX + (int64_t)ct.old * N;
     static_assert(HH_PER_SLOT == 1, "one unknown per thread");
-    double acc[1 + 2 * NS], acr[2 * NS];
+    double acc[1 + 2 * NS];
 #pragma unroll
     for (int k = 0; k < 1 + 2 * NS; ++k) acc[k] = 0.0;
-#pragma unroll
-    for (int k = 0; k < 2 * NS; ++k) acr[k] = 0.0;
     if (p < N) {
         double2 dr, dx, pv[NS];
 #pragma unroll
@@ -408,16 +357,23 @@ __global__ __launch_bounds__(HH_VWG) void k_idr_up(Ctx cx)
             if (i < ns) {
                 acc[1 + 2 * i] = acc[1 + 2 * i] + (pv[i].x * dr.x + pv[i].y * dr.y);
                 acc[2 + 2 * i] = acc[2 + 2 * i] + (pv[i].x * dr.y - pv[i].y * dr.x);
-                if (mode == 0) {
-                    acr[2 * i] = acr[2 * i] + (pv[i].x * rn.x + pv[i].y * rn.y);
-                    acr[1 + 2 * i] = acr[1 + 2 * i] + (pv[i].x * rn.y - pv[i].y * rn.x);
-                }
             }
         }
     }
     group_finish<1 + 2 * NS>(pd, tl.idx, acc);
     if (mode == 0) {
-        __syncthreads();
+        // P^H r, from this thread's own r and P again: the s start-up steps
+        // read them twice so that the other steps hold fewer registers
+        double acr[2 * NS];
+#pragma unroll
+        for (int i = 0; i < NS; ++i) {
+            acr[2 * i] = acr[1 + 2 * i] = 0.0;
+            if (i < ns && p < N) {
+                const double2 pv = ldg(Pm, (int64_t)i * N + p), rn = ldg(r, p);
+                acr[2 * i] = acr[2 * i] + (pv.x * rn.x + pv.y * rn.y);
+                acr[1 + 2 * i] = acr[1 + 2 * i] + (pv.x * rn.y - pv.y * rn.x);
+            }
+        }
         group_finish<2 * NS>(pd, tl.idx, acr, 1 + 2 * HH_MAX_S);
     }
 }

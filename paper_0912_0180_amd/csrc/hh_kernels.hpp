@@ -302,39 +302,31 @@ __device__ inline void stencil_band(const HView &h, const S *__restrict__ x, con
 // a reducing pass in the fixed pairwise order and advances the scalar state
 // ---------------------------------------------------------------------------
 #define HH_FIN_WG 1024            // threads of the finaliser
-#define HH_FIN_UNIT 128           // partials one wave sums in one load
+#define HH_FIN_LANE 8             // consecutive partials per lane
+#define HH_FIN_UNIT (64 * HH_FIN_LANE)   // partials one wave sums at a time
 #define HH_FIN_SUMS 8192          // unit sums kept in LDS at a time
 
 __device__ inline bool cfin(double2 v) { return isfinite(v.x) && isfinite(v.y); }
 
-__device__ inline void stop(SolveState *st, int reason)
-{
-    st->phase = PH_STOP;
-    st->reason = reason;
-}
-
-__device__ inline void record(const ProbDev *pd, SolveState *st, double rel)
-{
-    st->rel = rel;
-    if (pd->hist && st->mv - 1 < st->hist_len && st->mv >= 1) pd->hist[st->mv - 1] = rel;
-}
-
 typedef double hh_dvec2u __attribute__((ext_vector_type(2), aligned(8)));
 
-// Sums value first + q (q < nv) of the group partials, stored value-major
-// (part[v * n + c] for group c of n), each by the pairwise tree over the
-// zero-padded power-of-two length; results in out[q] (LDS), visible to every
-// thread.  A wave takes units of 128 consecutive partials: one 16-byte load
-// per lane (a value's partials start 8-byte aligned), the pair in the lane,
-// then the tree over the lanes (wave_sum).  An aligned power-of-two block of a
-// pairwise tree is itself a subtree, so the unit sums, kept in LDS, combine by
-// the rest of it, one wave per value.  Loads are whole lines: with a thread
-// loading its own block of up to 32 partials every load touched 64 lines, and
-// 9 values of 4096 partials took 30 us (now 2).
-__device__ inline void reduce_partials(const double *part, int n, int first, int nv, double *out)
+// Sums value first + q (q < nv) of n group partials, stored value-major
+// (part[v * stride + c]), each by the pairwise tree over the zero-padded
+// power-of-two length; results in out[q] (LDS), visible to every thread of the
+// NW waves.  A wave takes units of 512 consecutive partials: 8 per lane in four
+// 16-byte loads (a value's partials start 8-byte aligned), summed pairwise in
+// the lane, then the tree over the lanes (wave_sum).  An aligned power-of-two
+// block of a pairwise tree is itself a subtree, so the unit sums, kept in LDS,
+// combine by the rest of it, one wave per value.  With a thread loading its own
+// block of up to 32 partials each load touched 64 lines, with 2 per lane the
+// wave_sums' issue counted: 9 values of 4096 partials took 30 and 14 us, now
+// 9, the time one CU takes for 295 KB that other XCDs wrote (see k_red).
+template <int NW>
+__device__ __forceinline__ void reduce_partials(const double *part, int stride, int n, int first, int nv, double *out)
 {
     __shared__ double sums[HH_FIN_SUMS];
-    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6), nw = HH_FIN_WG / 64;
+    constexpr int B = 4, L = HH_FIN_LANE, nw = NW;      // B units in flight per wave
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
     const int U = (n + HH_FIN_UNIT - 1) / HH_FIN_UNIT;
     int per = 1;                       // unit sums per lane of the second step
     while (64 * per < U) per <<= 1;
@@ -343,26 +335,34 @@ __device__ inline void reduce_partials(const double *part, int n, int first, int
     auto value_of = [&](int g) { return __builtin_amdgcn_readfirstlane((int)(((float)g + 0.5f) * ru)); };
     for (int q0 = 0; q0 < nv; q0 += qstep) {
         const int nq = min(nv - q0, qstep), T = nq * U;
-        constexpr int B = 8;           // units in flight per wave
         for (int g0 = wave; g0 < T; g0 += B * nw) {
-            double2 v[B];
+            double v[B][L];
 #pragma unroll
             for (int b = 0; b < B; ++b) {
-                const int g = g0 + b * nw, q = value_of(g), e = (g - q * U) * HH_FIN_UNIT + 2 * lane;
-                const double *p = part + (int64_t)(first + q0 + q) * n;
-                v[b] = cmk<double>(0.0, 0.0);
-                if (g < T && e + 1 < n) {
-                    const hh_dvec2u w = *(const HH_GLOBAL hh_dvec2u *)(p + e);
-                    v[b] = cmk<double>(w.x, w.y);
-                } else if (g < T && e < n) {
-                    v[b].x = ldg(p, e);
+                const int g = min(g0 + b * nw, T - 1), q = value_of(g), e0 = (g - q * U) * HH_FIN_UNIT + L * lane;
+                const double *p = part + (int64_t)(first + q0 + q) * stride;
+                if (e0 + L <= n) {
+#pragma unroll
+                    for (int i = 0; i < L; i += 2) {
+                        const hh_dvec2u w = *(const HH_GLOBAL hh_dvec2u *)(p + e0 + i);
+                        v[b][i] = w.x;
+                        v[b][i + 1] = w.y;
+                    }
+                } else {
+#pragma unroll
+                    for (int i = 0; i < L; ++i) v[b][i] = e0 + i < n ? ldg(p, e0 + i) : 0.0;
                 }
             }
 #pragma unroll
             for (int b = 0; b < B; ++b) {
-                const int g = g0 + b * nw, q = value_of(g);
-                if (g >= T) break;
-                const double r = wave_sum(v[b].x + v[b].y);
+                const int g = g0 + b * nw;
+                if (g >= T) break;     // uniform over the wave
+                const int q = value_of(g);
+#pragma unroll
+                for (int w = 1; w < L; w <<= 1)
+#pragma unroll
+                    for (int i = 0; i < L; i += 2 * w) v[b][i] = v[b][i] + v[b][i + w];
+                const double r = wave_sum(v[b][0]);
                 if (lane == 0) sums[q * 64 * per + (g - q * U)] = r;
             }
         }
@@ -395,7 +395,7 @@ __device__ inline void mirror(Ctrl &c, const SolveState &st)
 }
 
 // defined with the IDR kernels
-__device__ void idr_finalize(const ProbDev *pd, int kind, bool gate);
+__device__ __forceinline__ void idr_finalize(const ProbDev *pd, int kind, bool gate, int ng);
 
 // Scalar state of a Bi-CGSTAB solve, copied to registers before the
 // reduction (its loads overlap the partial sums) and written back once.
@@ -438,12 +438,19 @@ __device__ inline bool fin_runs(int kind, int phase)
     return true;
 }
 
+// values a Bi-CGSTAB pass's finalisation sums
+__host__ __device__ inline int fin_values(int kind)
+{
+    return kind == FIN_BNORM || kind == FIN_TRUE ? 1 : kind == FIN_ALPHA ? 2 : kind == FIN_OMEGA ? 4 : 3;
+}
+
 // gate: skip the update unless fin_runs(kind, phase of the state block),
-// decided after the state and the partials are loaded
-__device__ __forceinline__ void finalize(const ProbDev *pd, int kind, bool gate)
+// decided after the state and the partials are loaded; ng: partials per value
+// left to sum
+__device__ __forceinline__ void finalize(const ProbDev *pd, int kind, bool gate, int ng)
 {
     if (kind >= FIN_IDR_OMEGA) {
-        idr_finalize(pd, kind, gate);
+        idr_finalize(pd, kind, gate, ng);
         return;
     }
     SolveState *st = pd->st;
@@ -468,10 +475,9 @@ __device__ __forceinline__ void finalize(const ProbDev *pd, int kind, bool gate)
     b.drift_stall = st->drift_stall;
     b.drift_grow = st->drift_grow;
     const int phase = b.phase;
-    const int nv = (kind == FIN_BNORM || kind == FIN_TRUE) ? 1 : (kind == FIN_ALPHA ? 2 : (kind == FIN_OMEGA ? 4 : 3));
-    const int first = (kind == FIN_BNORM || kind == FIN_TRUE) ? 2 : 0;
+    const int nv = fin_values(kind), first = (kind == FIN_BNORM || kind == FIN_TRUE) ? 2 : 0;
     __shared__ double res[4];
-    reduce_partials(pd->part, pd->ngroup, first, nv, res);
+    reduce_partials<HH_FIN_WG / 64>(pd->part, pd->ngroup, ng, first, nv, res);
     const double *s = res;
     if (threadIdx.x != 0) return;
     if (gate && !fin_runs(kind, phase)) return;
@@ -614,14 +620,15 @@ __device__ inline void group_finish(const ProbDev *pd, int grp, double (&acc)[NV
 }
 
 // One workgroup per problem: sums the chunk partials of the pass just run and
-// advances the scalar state (kind = FinKind).
-__global__ __launch_bounds__(HH_FIN_WG) void k_fin(Ctx cx, const int *__restrict__ probs, int kind)
+// advances the scalar state (kind = FinKind).  red: k_red has left one partial
+// per value.
+__global__ __launch_bounds__(HH_FIN_WG) void k_fin(Ctx cx, const int *__restrict__ probs, int kind, int red)
 {
     const int prob = probs ? probs[blockIdx.x] : 0;
     const ProbDev *pd = cx.P + prob;
     // the control block mirrors the phase of the state block; one load
     if (!fin_runs(kind, phase_of(cx, prob))) return;
-    finalize(pd, kind, false);
+    finalize(pd, kind, false, red ? 1 : pd->ngroup);
 }
 
 // k_fin of a one-problem plan: the problem descriptor comes by value, so the
@@ -630,9 +637,40 @@ __global__ __launch_bounds__(HH_FIN_WG) void k_fin(Ctx cx, const int *__restrict
 // dependent round trips to memory the other XCDs wrote); the phase gate is
 // applied after them, on the state block's phase (which the control block
 // mirrors).
-__global__ __launch_bounds__(HH_FIN_WG) void k_fin1(int kind, ProbDev pv)
+__global__ __launch_bounds__(HH_FIN_WG) void k_fin1(int kind, ProbDev pv, int red)
 {
-    finalize(&pv, kind, true);
+    // nothing to sum: an IDR step k >= 1 has its omega (the control block
+    // mirrors the step's mode)
+    if (kind == FIN_IDR_OMEGA && ((const HH_GLOBAL int *)pv.ctrl)[1] == 2) return;
+    finalize(&pv, kind, true, red ? 1 : pv.ngroup);
+}
+
+// Many partials: one workgroup per value and problem (blockIdx.x, .y) leaves
+// the value's sum in place of its first partial, so that the finaliser's one
+// CU has as many values to read as the pass has.  One CU takes 9 us for the 9
+// x 4096 partials of IDR(4) at 128^3; these workgroups and their launch take
+// 4.  Used above HH_RED_MIN partials (below, the launch costs what it saves).
+#define HH_RED_MIN 16384
+#define HH_RED_WG 256
+__global__ __launch_bounds__(HH_RED_WG) void k_red(Ctx cx, const int *__restrict__ probs, int kind)
+{
+    const int prob = probs ? probs[blockIdx.y] : 0;
+    const ProbDev *pd = cx.P + prob;
+    const int v = (int)blockIdx.x;
+    const HH_GLOBAL int *ct = cx.ctrl ? (const HH_GLOBAL int *)(cx.ctrl + prob) : nullptr;
+    if (ct && !fin_runs(kind, ct[0])) return;
+    int value = v;
+    if (kind >= FIN_IDR_OMEGA) {
+        // the values this step's mode sums (idr_finalize)
+        const int mode = ct ? ct[1] : 0, ns = pd->nidr;
+        if (kind == FIN_IDR_OMEGA ? mode == 2 : !(v < 1 + 2 * ns || (mode == 0 && v >= 1 + 2 * HH_MAX_S && v < 1 + 2 * HH_MAX_S + 2 * ns)))
+            return;
+    } else if (kind == FIN_BNORM || kind == FIN_TRUE) {
+        value = 2;
+    }
+    __shared__ double res[1];
+    reduce_partials<HH_RED_WG / 64>(pd->part, pd->ngroup, pd->ngroup, value, 1, res);
+    if (threadIdx.x == 0) pd->part[(int64_t)value * pd->ngroup] = res[0];
 }
 
 // ---------------------------------------------------------------------------

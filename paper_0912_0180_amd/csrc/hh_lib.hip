@@ -1233,12 +1233,23 @@ void launch_vcycle(const Plan &pl, int fsel, int osel, const void *fptr, void *o
 
 void launch_fin(const Plan &pl, const int *probs, int n, int kind, hipStream_t s)
 {
-    if (pl.count == 1 && !pl.host.empty()) {
-        if (n > 0) hipLaunchKernelGGL(k_fin1, dim3(1), dim3(HH_FIN_WG), 0, s, kind, pl.host[0]);
-        return;
-    }
+    if (n <= 0) return;
     const Ctx c = ctx_of(pl, pl.chunks);
-    if (n > 0) hipLaunchKernelGGL(k_fin, dim3(n), dim3(HH_FIN_WG), 0, s, c, pl.count == 1 ? nullptr : probs, kind);
+    // many partials are summed per value by workgroups of their own first
+    int ng = 0, ns = 0;
+    for (const ProbDev &p : pl.host) {
+        ng = std::max(ng, p.ngroup);
+        ns = std::max(ns, p.nidr);
+    }
+    const bool step = kind == FIN_IDR_STEP;
+    const int nv = step ? 1 + 2 * ns : kind == FIN_IDR_OMEGA ? 3 : fin_values(kind);
+    const int red = kind != FIN_IDR_INIT && (int64_t)nv * ng >= HH_RED_MIN ? 1 : 0;
+    const int *pr = pl.count == 1 ? nullptr : probs;
+    if (red) hipLaunchKernelGGL(k_red, dim3(step ? 1 + 2 * HH_MAX_S + 2 * ns : nv, n), dim3(HH_RED_WG), 0, s, c, pr, kind);
+    if (pl.count == 1 && !pl.host.empty())
+        hipLaunchKernelGGL(k_fin1, dim3(1), dim3(HH_FIN_WG), 0, s, kind, pl.host[0], red);
+    else
+        hipLaunchKernelGGL(k_fin, dim3(n), dim3(HH_FIN_WG), 0, s, c, pr, kind, red);
 }
 
 template <int DIM, typename SP>

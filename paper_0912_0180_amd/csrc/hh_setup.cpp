@@ -470,7 +470,7 @@ hh_status desc_check(const hh_grid_desc *d, int &levels, int &coarse, std::strin
         }
         N *= d->n[a];
     }
-    // (the finaliser keeps one sum per 65,536 unknowns in LDS, 8192 at most)
+    // (the finaliser keeps one sum per 262,144 unknowns in LDS, 8192 at most)
     if (N > ((int64_t)1 << 28)) { err = "more than 2^28 unknowns"; return HH_ERR_ARG; }
     if (d->centering == HH_VERTEX) {
         // the operator of Sec. 3 on its vertex grid: no multigrid hierarchy
