@@ -2323,9 +2323,11 @@ __global__ __launch_bounds__(HH_ILU_ROWS_WG, 1) void k_ilu_up_rows(Ctx cx, IluAr
 }
 
 // ---------------------------------------------------------------------------
-// Merged 2D legs of K consecutive coarse levels lev0 .. lev0 + K - 1 (ending
-// at the tail's first level lev0 + K), one launch per leg instead of K.  On
-// these small levels a launch costs its latency, not its work.
+// Merged 2D legs of K consecutive levels lev0 .. lev0 + K - 1 (ending at the
+// tail's first level, or a coarsest level that k_coarse solves, lev0 + K), one
+// launch per leg instead of K.  On these small levels a launch costs its
+// latency, not its work.  f0, e0: level lev0's right-hand side (of type TF:
+// the cycle's input on level 0) and result.
 //
 // Down: the smoothing from zero is pointwise, so a coarse point's restricted
 // residual depends only on the finer level within two points of its
@@ -2391,8 +2393,8 @@ template <int K> __device__ __forceinline__ int mdown_origin(int c0, int k)
     return (c0 << (K - k)) - 2 * ((1 << (K - k)) - 1);
 }
 
-template <typename T, int K, int C, int NT>
-__global__ __launch_bounds__(NT) void k_vdown_m(Ctx cx, LvChain<T, K> lc)
+template <typename T, typename TF, int K, int C, int NT>
+__global__ __launch_bounds__(NT) void k_vdown_m(Ctx cx, LvChain<T, K> lc, const void *f0)
 {
     using Cx = V2<T>;
     using MD = MergeDown<K, C>;
@@ -2430,7 +2432,7 @@ __global__ __launch_bounds__(NT) void k_vdown_m(Ctx cx, LvChain<T, K> lc)
             pr[q] = 0;
             if (l < N0 && gx >= 0 && gx < nx && gy >= 0 && gy < ny) {
                 const int64_t p = gx + (int64_t)nx * gy;
-                fr[q] = ldg(lc.L[0].f, p);
+                fr[q] = ccvt<T>(ldg((const TF *)f0, p));
                 pr[q] = ldg(lc.L[0].phi, p);
             }
         }
@@ -2586,8 +2588,8 @@ __global__ __launch_bounds__(NT) void k_vdown_m(Ctx cx, LvChain<T, K> lc)
     }
 }
 
-template <typename T, int K, int UT, int NT>
-__global__ __launch_bounds__(NT) void k_vup_m(Ctx cx, LvChain<T, K> lc)
+template <typename T, typename TF, int K, int UT, int NT>
+__global__ __launch_bounds__(NT) void k_vup_m(Ctx cx, LvChain<T, K> lc, const void *f0, void *e0)
 {
     using Cx = V2<T>;
     using MU = MergeUp<K, UT>;
@@ -2638,7 +2640,7 @@ __global__ __launch_bounds__(NT) void k_vup_m(Ctx cx, LvChain<T, K> lc)
             pr[k][q] = 0;
             if (l < R * R && lx < wx[k] + 2 && ly < wy[k] + 2 && gx >= 0 && gx < nx && gy >= 0 && gy < ny) {
                 const int64_t p = gx + (int64_t)nx * gy;
-                fr[k][q] = ldg(lc.L[k].f, p);
+                fr[k][q] = k == 0 ? ccvt<T>(ldg((const TF *)f0, p)) : ldg(lc.L[k].f, p);
                 pr[k][q] = ldg(lc.L[k].phi, p);
             }
         }
@@ -2754,7 +2756,7 @@ __global__ __launch_bounds__(NT) void k_vup_m(Ctx cx, LvChain<T, K> lc)
                 u = cmadd<T>(U[l], gw, csub<T>(Fk[l], mu));
             }
             if (k == 0) {
-                if (in) stg(lc.L[0].e, gx + (int64_t)nx * gy, u);
+                if (in) stg((Cx *)e0, gx + (int64_t)nx * gy, u);
             } else {
                 Eo[ix + WO * iy] = u;
             }

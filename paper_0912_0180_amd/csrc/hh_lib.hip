@@ -396,16 +396,30 @@ template <typename T> struct MergeTile;
 template <> struct MergeTile<float> { static constexpr int C = 2, UT = 16, UT4 = 32, NT = 1024; };
 template <> struct MergeTile<double> { static constexpr int C = 2, UT = 16, UT4 = 32, NT = 1024; };
 
+// Level 0 takes part on grids of at most HH_MERGE_TOP points (its legs are then
+// latency too: 128^2 FP64 cycle 32 -> 21 us with the next rule), and where
+// k_coarse solves the coarsest level the merged legs end there: the tail
+// kernel's two launches beside it cost more than two more merged levels.
+#define HH_MERGE_TOP 65536
+static bool merges(const hh_grid *const *G, int count)
+{
+    if (const char *e = getenv("HH_MERGE"))
+        if (atoi(e) == 0) return false;
+    return count == 1 && G[0]->hs.dim == 2 && !G[0]->host_only && G[0]->hs.coarse_op != HH_COARSE_GALERKIN &&
+           G[0]->hs.smoother != HH_SMOOTH_ILU0;
+}
+// first level below the tiled and merged legs of a plan's problem g
+static int plan_tail(const hh_grid *g, int count, bool fp32)
+{
+    return merges(&g, count) && coarse_split(g->hs) ? g->hs.nlev - 1 : tail_level(g->hs, fp32);
+}
 static void plan_merge(Plan &pl, const hh_grid *const *G, int count, bool fp32)
 {
     pl.mK = pl.mlev0 = pl.mdn = pl.mKup = pl.mlev0u = pl.mup = 0;
-    if (const char *e = getenv("HH_MERGE"))
-        if (atoi(e) == 0) return;
-    if (count != 1 || G[0]->hs.dim != 2 || G[0]->host_only || G[0]->hs.coarse_op == HH_COARSE_GALERKIN ||
-        G[0]->hs.smoother == HH_SMOOTH_ILU0)
-        return;
+    if (!merges(G, count)) return;
     const HostSetup &hs = G[0]->hs;
-    const int t = tail_level(hs, fp32), K = std::min(3, t - 1), Kup = std::min(4, t - 1);
+    const int t = plan_tail(G[0], count, fp32), most = hs.lev[0].N <= HH_MERGE_TOP ? t : t - 1;
+    const int K = std::min(3, most), Kup = std::min(4, most);
     if (K < 2) return;
     for (int l = t - Kup; l < t; ++l)
         if (hs.lev[l].n[0] != 2 * hs.lev[l + 1].n[0] || hs.lev[l].n[1] != 2 * hs.lev[l + 1].n[1]) return;
@@ -641,14 +655,14 @@ hh_status plan_build(Plan &pl, const std::vector<const hh_grid *> &G, bool fp32)
         if (pl.mK && l >= pl.mlev0) continue;   // merged levels (mlev0u <= mlev0)
         const hh_grid *rep = nullptr;
         for (const hh_grid *g : G)
-            if (l < tail_level(g->hs, fp32) && (!rep || g->hs.lev[l].N > rep->hs.lev[l].N)) rep = g;
+            if (l < plan_tail(g, (int)G.size(), fp32) && (!rep || g->hs.lev[l].N > rep->hs.lev[l].N)) rep = g;
         if (!rep || rep->host_only) continue;
         pl.vdv[l] = tune_leg(rep, fp32, 0, l);
         if (!pl.mK || l < pl.mlev0u) pl.vuv[l] = tune_leg(rep, fp32, 1, l);
     }
     for (int q = 0; q < pl.count; ++q) {
         const HostSetup &hs = G[q]->hs;
-        const int t = tail_level(hs, fp32);
+        const int t = plan_tail(G[q], pl.count, fp32);
         pl.Lmax = std::max(pl.Lmax, t);
         const bool split = coarse_split(hs);
         if (split) {
@@ -1006,7 +1020,7 @@ static void plan_host_one(Plan &pl, const hh_grid *g, bool fp32, const void *L1,
     pl.fp32 = fp32;
     const hh_grid *G[1] = {g};
     plan_merge(pl, G, 1, fp32);
-    const int t = tail_level(hs, fp32);
+    const int t = plan_tail(g, 1, fp32);
     pl.Lmax = t;
     for (int l = 0; l < HH_MAXLEV; ++l) {
         pl.vdv[l] = pl.vuv[l] = 0;
@@ -1045,30 +1059,39 @@ static void plan_host_one(Plan &pl, const hh_grid *g, bool fp32, const void *L1,
     pl.lv32h = lv32h;
 }
 
-// the merged down- (leg 0) or up-leg (leg 1) of a one-problem 2D plan
-template <typename T, int K>
-static void launch_merged_k(int leg, const Plan &pl, hipStream_t s, const LevelDev<T> *L)
+// the merged down- (leg 0) or up-leg (leg 1) of a one-problem 2D plan; fptr,
+// optr: the cycle's input and output
+template <typename T, typename TF, int K>
+static void launch_merged_k(int leg, const Plan &pl, hipStream_t s, const LevelDev<T> *L, const void *fptr, void *optr)
 {
     LvChain<T, K> lc;
     const int l0 = leg == 0 ? pl.mlev0 : pl.mlev0u;
     for (int k = 0; k <= K; ++k) lc.L[k] = L[l0 + k];
+    const void *f0 = l0 == 0 ? fptr : (const void *)L[l0].f;
+    void *e0 = l0 == 0 ? optr : (void *)L[l0].e;
     const Ctx c = ctx_of(pl, pl.chunks);
     constexpr int NT = MergeTile<T>::NT;
     constexpr int UT = K == 4 ? MergeTile<T>::UT4 : MergeTile<T>::UT;
     if (leg == 0) {
-        if constexpr (K <= 3) hipLaunchKernelGGL((k_vdown_m<T, K, MergeTile<T>::C, NT>), dim3(pl.mdn), dim3(NT), 0, s, c, lc);
+        if constexpr (K <= 3) hipLaunchKernelGGL((k_vdown_m<T, TF, K, MergeTile<T>::C, NT>), dim3(pl.mdn), dim3(NT), 0, s, c, lc, f0);
     } else {
-        hipLaunchKernelGGL((k_vup_m<T, K, UT, NT>), dim3(pl.mup), dim3(NT), 0, s, c, lc);
+        hipLaunchKernelGGL((k_vup_m<T, TF, K, UT, NT>), dim3(pl.mup), dim3(NT), 0, s, c, lc, f0, e0);
     }
 }
+template <typename T, typename TF>
+static void launch_merged_t(int leg, const Plan &pl, hipStream_t s, const LevelDev<T> *L, const void *fptr, void *optr)
+{
+    const int K = leg == 0 ? pl.mK : pl.mKup;
+    if (K == 2) launch_merged_k<T, TF, 2>(leg, pl, s, L, fptr, optr);
+    else if (K == 3) launch_merged_k<T, TF, 3>(leg, pl, s, L, fptr, optr);
+    else launch_merged_k<T, TF, 4>(leg, pl, s, L, fptr, optr);
+}
 template <typename T>
-static void launch_merged(int leg, const Plan &pl, hipStream_t s, const LvHost &lh)
+static void launch_merged(int leg, const Plan &pl, hipStream_t s, const LvHost &lh, const void *fptr, void *optr)
 {
     const LevelDev<T> *L = lv_of<T>(lh);
-    const int K = leg == 0 ? pl.mK : pl.mKup;
-    if (K == 2) launch_merged_k<T, 2>(leg, pl, s, L);
-    else if (K == 3) launch_merged_k<T, 3>(leg, pl, s, L);
-    else launch_merged_k<T, 4>(leg, pl, s, L);
+    if ((leg == 0 ? pl.mlev0 : pl.mlev0u) == 0) launch_merged_t<T, double2>(leg, pl, s, L, fptr, optr);
+    else launch_merged_t<T, V2<T>>(leg, pl, s, L, fptr, optr);
 }
 
 // the fused legs of Galerkin level l >= 1 of a one-problem 2D plan (leg 0
@@ -1153,7 +1176,7 @@ static void vcycle_t(const Plan &pl, int fsel, int osel, const void *fptr, void 
         if (pl.galerkin && l >= 1) launch_gal_leg<T>(0, pl, l, s, lh);
         else launch_leg<DIM, T>(0, pl.vdv[l], pl.down[l].n, s, ctx_of(pl, pl.down[l]), l, fsel, osel, fptr, optr, lh);
     }
-    if (pl.mK) launch_merged<T>(0, pl, s, lh);
+    if (pl.mK) launch_merged<T>(0, pl, s, lh, fptr, optr);
     {
         // coarse part: tail kernel (whole, or down-legs of split problems),
         // multi-workgroup coarsest solves, up-legs of split problems
@@ -1177,7 +1200,7 @@ static void vcycle_t(const Plan &pl, int fsel, int osel, const void *fptr, void 
                 hipLaunchKernelGGL((k_vtail<DIM, T, false>), dim3(pl.nfin), dim3(TailCap<T>::WG), 0, s, c, probs, 1, TailArgs<T>{});
         }
     }
-    if (pl.mK) launch_merged<T>(1, pl, s, lh);
+    if (pl.mK) launch_merged<T>(1, pl, s, lh, fptr, optr);
     if constexpr (DIM == 2 && std::is_same<T, double>::value) {
         if (pl.ilu) {
             // ILU(0) up-legs (one problem): one workgroup per level
@@ -1613,18 +1636,26 @@ hh_status hh_profile_vcycle(const hh_grid *g, hh_prec prec, const void *f, void 
     lh.d = pl.lv64h;
     lh.f = pl.lv32h;
     const Ctx cd = ctx_of(pl, pl.down[0]), cu = ctx_of(pl, pl.up[0]);
-    launch_vcycle(pl, VS_IN, VS_OUT, f, u, s);   // warm-up; leaves every level's f and e valid
+    // the finest legs as launches of their own, also where the cycle merges
+    // them with the next levels'
+    const bool md = pl.mK && pl.mlev0 == 0, mu = pl.mK && pl.mlev0u == 0;
+    const int vd = md ? tune_leg(g, fp32, 0, 0) : pl.vdv[0], vu = mu ? tune_leg(g, fp32, 1, 0) : pl.vuv[0];
+    int nd = pl.down[0].n, nu = pl.up[0].n, other;
+    if (md) vtile_counts(g->hs.dim, vd, g->hs.lev[0], g->hs.lev[1], nd, other);
+    if (mu) vtile_counts(g->hs.dim, vu, g->hs.lev[0], g->hs.lev[1], other, nu);
+    launch_vcycle(pl, VS_IN, VS_OUT, f, u, s);   // warm-up
     hipError_t e = hipEventRecord(ev[0], s);
     for (int r = 0; r < reps; ++r) launch_vcycle(pl, VS_IN, VS_OUT, f, u, s);
     if (e == hipSuccess) e = hipEventRecord(ev[1], s);
     if (e == hipSuccess) e = hipEventRecord(ev[2], s);
     for (int r = 0; r < reps; ++r)
-        launch_leg_any(g->hs.dim, fp32, 0, pl.vdv[0], pl.down[0].n, s, cd, 0, VS_IN, VS_OUT, f, u, lh);
+        launch_leg_any(g->hs.dim, fp32, 0, vd, nd, s, cd, 0, VS_IN, VS_OUT, f, u, lh);
     if (e == hipSuccess) e = hipEventRecord(ev[3], s);
     if (e == hipSuccess) e = hipEventRecord(ev[4], s);
     for (int r = 0; r < reps; ++r)
-        launch_leg_any(g->hs.dim, fp32, 1, pl.vuv[0], pl.up[0].n, s, cu, 0, VS_IN, VS_OUT, f, u, lh);
+        launch_leg_any(g->hs.dim, fp32, 1, vu, nu, s, cu, 0, VS_IN, VS_OUT, f, u, lh);
     if (e == hipSuccess) e = hipEventRecord(ev[5], s);
+    if (mu) launch_vcycle(pl, VS_IN, VS_OUT, f, u, s);   // u = V(f) (merged legs leave no e on level 1)
     if (e == hipSuccess) e = hipGetLastError();
     if (e == hipSuccess) e = hipEventSynchronize(ev[5]);
     float ms[3] = {0.f, 0.f, 0.f};
@@ -1634,10 +1665,10 @@ hh_status hh_profile_vcycle(const hh_grid *g, hh_prec prec, const void *f, void 
     out->vcycle_us = 1e3 * ms[0] / reps;
     out->down_us = 1e3 * ms[1] / reps;
     out->up_us = 1e3 * ms[2] / reps;
-    out->down_shape = pl.vdv[0];
-    out->up_shape = pl.vuv[0];
-    out->down_groups = pl.down[0].n;
-    out->up_groups = pl.up[0].n;
+    out->down_shape = vd;
+    out->up_shape = vu;
+    out->down_groups = nd;
+    out->up_groups = nu;
     return HH_OK;
 }
 
