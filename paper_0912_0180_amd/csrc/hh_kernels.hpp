@@ -1584,7 +1584,9 @@ constexpr int GAL_NT = 256;
 // Down-leg: u1 = g f on the fine box (the owned 2C x 2C cells and a ring of
 // three: the residual's stencil reaches two cells beyond the restriction's
 // footprint), r = f - G u1 on the footprint (owned cells and a ring of one),
-// full weighting onto the C x C coarse tile.
+// full weighting onto the C x C coarse tile.  Without pre-smoothing r is f
+// itself, so the 25 stencil entries per point are not read (640^2 FP64: 42 ->
+// 9 us).
 template <typename T>
 __global__ __launch_bounds__(GAL_NT) void k_gdown(Ctx cx, GalArgs<T> ga)
 {
@@ -1599,10 +1601,10 @@ __global__ __launch_bounds__(GAL_NT) void k_gdown(Ctx cx, GalArgs<T> ga)
     const int f0x = 2 * c0x, f0y = 2 * c0y;
     const int64_t N = (int64_t)nfx * nfy;
     const C zero = cmk<T>(0, 0);
-    for (int l = threadIdx.x; l < BX * BX; l += GAL_NT) {
+    for (int l = threadIdx.x; ga.pre && l < BX * BX; l += GAL_NT) {
         const int gx = f0x - 3 + l % BX, gy = f0y - 3 + l / BX;
         C u1 = zero;
-        if (ga.pre && gx >= 0 && gx < nfx && gy >= 0 && gy < nfy) {
+        if (gx >= 0 && gx < nfx && gy >= 0 && gy < nfy) {
             const int64_t p = gx + (int64_t)nfx * gy;
             u1 = cmul<T>(jweight<T>(ldg(ga.G, 12 * N + p), ga.omega), ldg(ga.f, p));
         }
@@ -1615,14 +1617,17 @@ __global__ __launch_bounds__(GAL_NT) void k_gdown(Ctx cx, GalArgs<T> ga)
         C res = zero;
         if (gx >= 0 && gx < nfx && gy >= 0 && gy < nfy) {
             const int64_t p = gx + (int64_t)nfx * gy;
-            const int c = (rx + 2) + BX * (ry + 2);
-            C mu = cmul<T>(ldg(ga.G, 12 * N + p), U[c]);
+            res = ldg(ga.f, p);
+            if (ga.pre) {
+                const int c = (rx + 2) + BX * (ry + 2);
+                C mu = cmul<T>(ldg(ga.G, 12 * N + p), U[c]);
 #pragma unroll
-            for (int s = 0; s < 25; ++s) {
-                if (s == 12) continue;
-                mu = cmadd<T>(mu, ldg(ga.G, s * N + p), U[c + (s % 5 - 2) + BX * (s / 5 - 2)]);
+                for (int s = 0; s < 25; ++s) {
+                    if (s == 12) continue;
+                    mu = cmadd<T>(mu, ldg(ga.G, s * N + p), U[c + (s % 5 - 2) + BX * (s / 5 - 2)]);
+                }
+                res = csub<T>(res, mu);
             }
-            res = csub<T>(ldg(ga.f, p), mu);
         }
         R[l] = res;
     }
@@ -1729,26 +1734,28 @@ struct IluArgs {
     double omega;                     // relaxation of the ILU(0) update
     int inner;                        // 1: the sweep kernel runs the pointwise phases too;
                                       // 0: k_ilu_prolong, k_ilu_resid, k_ilu_update run them
-    int diag;                         // 1: w in the row form's step order (IluLayout position
-                                      // dd TS + t of each point); 0: w by point
     uint64_t *chan;                   // row form: its channel (IluLayout::chan_words words)
 };
 
 // entry s (offset (s % 5 - 2, s / 5 - 2)) of row p of M_l applied to u, with
 // the neighbour outside the grid taken as zero: the Galerkin stencil, or the
 // 5-point set of the rediscretised stencil; y = M u in the contract's order
-__device__ __forceinline__ double2 ilu_Mu(const LevelDev<double> &L, const double2 *u, int i, int j, int64_t p)
+// (reads clamped to the grid and masked, so that they issue together: a
+// branch per entry made 25 round trips of them)
+template <bool GAL> __device__ __forceinline__ double2 ilu_Mu(const LevelDev<double> &L, const double2 *u, int i, int j, int64_t p)
 {
     const int nx = L.n[0], ny = L.n[1];
     const double2 zero = cmk<double>(0.0, 0.0);
-    if (L.g) {
+    if (GAL) {
         const int64_t N = L.N;
         double2 t = cmul<double>(ldg(L.g, 12 * N + p), ldg(u, p));
+#pragma unroll
         for (int s = 0; s < 25; ++s) {
             if (s == 12) continue;
             const int ii = i + s % 5 - 2, jj = j + s / 5 - 2;
-            const double2 uq = (ii >= 0 && ii < nx && jj >= 0 && jj < ny) ? ldg(u, ii + (int64_t)nx * jj) : zero;
-            t = cadd<double>(t, cmul<double>(ldg(L.g, s * N + p), uq));
+            const bool in = ii >= 0 && ii < nx && jj >= 0 && jj < ny;
+            const double2 uq = ldg(u, in ? ii + (int64_t)nx * jj : p);
+            t = cadd<double>(t, cmul<double>(ldg(L.g, s * N + p), in ? uq : zero));
         }
         return t;
     }
@@ -1819,23 +1826,6 @@ template <bool GAL> struct IluLayout {
     __host__ __device__ int64_t chan_words() const { return 1 + 2 * (int64_t)nb * nx * S::HR * 4; }
 };
 
-// position of point p in w: p, or with the row form the point's layout
-// position (the level's set: the 25-point one on Galerkin levels)
-__device__ __forceinline__ int64_t ilu_wpos(const IluArgs &a, int64_t p)
-{
-    if (!a.diag) return p;
-    const int nx = a.fl.n[0], ny = a.fl.n[1];
-    const int i = (int)(p % nx), j = (int)(p / nx);
-    if (a.fl.g) {
-        const IluLayout<true> lay(nx, ny);
-        const int b = lay.band_of(j), r = j - lay.j0(b);
-        return (lay.d0(b) + i + 3 * r) * lay.TS + r;
-    }
-    const IluLayout<false> lay(nx, ny);
-    const int b = lay.band_of(j), r = j - lay.j0(b);
-    return (lay.d0(b) + i + r) * lay.TS + r;
-}
-
 // the pointwise phases of the up-leg at point p: u = 0 + P e_{l+1} (bilinear,
 // x then y; coarse values outside are zero), r = f - M u (into w, once every
 // u is written), and after the solves u = u + omega z
@@ -1844,7 +1834,7 @@ __device__ __forceinline__ void ilu_prolong_at(const IluArgs &a, int64_t p)
     const int nx = a.fl.n[0], ncx = a.cl.n[0], ncy = a.cl.n[1];
     const double2 *__restrict__ ec = a.cl.e;
     const double2 zero = cmk<double>(0.0, 0.0);
-    const int i = (int)(p % nx), j = (int)(p / nx);
+    const int j = (int)fdiv((uint32_t)p, a.fl.fx), i = (int)p - j * nx;
     const int Ix = i >> 1, Iox = (i & 1) ? Ix + 1 : Ix - 1;
     const int Iy = j >> 1, Ioy = (j & 1) ? Iy + 1 : Iy - 1;
     auto ev = [&](int x, int y) -> double2 {
@@ -1857,12 +1847,12 @@ __device__ __forceinline__ void ilu_prolong_at(const IluArgs &a, int64_t p)
 __device__ __forceinline__ void ilu_resid_at(const IluArgs &a, int64_t p)
 {
     const int nx = a.fl.n[0];
-    const int i = (int)(p % nx), j = (int)(p / nx);
-    stg(a.fl.w, ilu_wpos(a, p), csub<double>(ldg(a.f, p), ilu_Mu(a.fl, a.u, i, j, p)));
+    const int j = (int)fdiv((uint32_t)p, a.fl.fx), i = (int)p - j * nx;
+    stg(a.fl.w, p, csub<double>(ldg(a.f, p), a.fl.g ? ilu_Mu<true>(a.fl, a.u, i, j, p) : ilu_Mu<false>(a.fl, a.u, i, j, p)));
 }
 __device__ __forceinline__ void ilu_update_at(const IluArgs &a, int64_t p)
 {
-    stg(a.u, p, crsadd<double>(ldg(a.u, p), a.omega, ldg(a.fl.w, ilu_wpos(a, p))));
+    stg(a.u, p, crsadd<double>(ldg(a.u, p), a.omega, ldg(a.fl.w, p)));
 }
 
 // the pointwise phases as grid-wide launches, for levels whose points are
@@ -1878,13 +1868,54 @@ __global__ __launch_bounds__(HH_ILU_PW) void k_ilu_resid(Ctx cx, IluArgs a)
     if (phase_of(cx, 0) != PH_RUN) return;
     const int64_t p = blockIdx.x * (int64_t)HH_ILU_PW + threadIdx.x;
     if (p < a.fl.N) ilu_resid_at(a, p);
-    if (p == 0 && a.diag) a.chan[0] = a.chan[0] + 1;   // the solves' launch number
 }
 __global__ __launch_bounds__(HH_ILU_PW) void k_ilu_update(Ctx cx, IluArgs a)
 {
     if (phase_of(cx, 0) != PH_RUN) return;
     const int64_t p = blockIdx.x * (int64_t)HH_ILU_PW + threadIdx.x;
     if (p < a.fl.N) ilu_update_at(a, p);
+}
+
+// The residual into, and the update from, w in the row form's step order.  A
+// workgroup takes SK steps of one band: threads run along the rows of u
+// and f, w goes through LDS, so both sides are read and written in whole lines
+// (by point, every thread's w lies a step, 512 or 1024 bytes, from the next
+// one's: 1280^2 residual 40 us, update 37 us).
+template <bool GAL> __host__ __device__ constexpr int ilu_skew_steps() { return GAL ? 8 : 16; }   // 25 terms: one point per thread
+template <bool GAL, bool UPDATE>
+__global__ __launch_bounds__(HH_ILU_PW) void k_ilu_skew(Ctx cx, IluArgs a, int tiles)
+{
+    using S = IluSet<GAL>;
+    constexpr int SK = ilu_skew_steps<GAL>(), RW = S::RW, LD = RW + 1, NP = SK * RW / HH_ILU_PW;
+    static_assert(SK * RW % HH_ILU_PW == 0, "whole points per thread");
+    __shared__ double2 t[SK * LD];
+    if (phase_of(cx, 0) != PH_RUN) return;
+    const int nx = a.fl.n[0];
+    const IluLayout<GAL> lay(nx, a.fl.n[1]);
+    const int b = (int)blockIdx.x / tiles, j0 = lay.j0(b), R = lay.j0(b + 1) - j0, nd = nx + S::M * (R - 1), s0 = ((int)blockIdx.x - b * tiles) * SK;
+    if (!UPDATE && blockIdx.x == 0 && threadIdx.x == 0) a.chan[0] = a.chan[0] + 1;   // the solves' launch number
+    if (s0 >= nd) return;      // uniform
+    double2 *w = a.fl.w + (lay.d0(b) + s0) * RW;
+    const int nw = min(SK, nd - s0) * RW;
+    if (UPDATE) {
+        for (int e = threadIdx.x; e < nw; e += HH_ILU_PW) t[e / RW * LD + e % RW] = ldg(w, e);
+        __syncthreads();
+    }
+#pragma unroll
+    for (int q = 0; q < NP; ++q) {
+        const int e = (int)threadIdx.x + q * HH_ILU_PW, s = e % SK, r = e / SK, i = s0 + s - S::M * r;
+        double2 v = cmk<double>(0.0, 0.0);
+        if (r < R && i >= 0 && i < nx) {
+            const int64_t p = i + (int64_t)nx * (j0 + r);
+            if (UPDATE) stg(a.u, p, crsadd<double>(ldg(a.u, p), a.omega, t[s * LD + r]));
+            else v = csub<double>(ldg(a.f, p), ilu_Mu<GAL>(a.fl, a.u, i, j0 + r, p));
+        }
+        if (!UPDATE) t[s * LD + r] = v;
+    }
+    if (!UPDATE) {
+        __syncthreads();
+        for (int e = threadIdx.x; e < nw; e += HH_ILU_PW) stg(w, e, t[e / RW * LD + e % RW]);
+    }
 }
 
 __global__ __launch_bounds__(HH_ILU_WG) void k_ilu_up(Ctx cx, IluArgs a)

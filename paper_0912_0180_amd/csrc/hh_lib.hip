@@ -1159,6 +1159,20 @@ template <bool GAL> static int ilu_groups(int nx, int ny)
     return std::min(std::min(IluLayout<GAL>(nx, ny).nb, 2 + nx / (S::M * S::RW)), 32);
 }
 
+// residual, solves and update of one level in the row form
+template <bool GAL> static void launch_ilu_rows(const Ctx &c, const IluArgs &a, hipStream_t s)
+{
+    using S = IluSet<GAL>;
+    const int nx = a.fl.n[0], ny = a.fl.n[1];
+    const IluLayout<GAL> lay(nx, ny);
+    const int rmax = lay.base + (lay.extra > 0 ? 1 : 0);
+    const int tiles = ceil_div(nx + S::M * (rmax - 1), ilu_skew_steps<GAL>());
+    const dim3 sg((unsigned)tiles * (unsigned)lay.nb);
+    hipLaunchKernelGGL((k_ilu_skew<GAL, false>), sg, dim3(HH_ILU_PW), 0, s, c, a, tiles);
+    hipLaunchKernelGGL(k_ilu_up_rows<GAL>, dim3(ilu_groups<GAL>(nx, ny)), dim3(HH_ILU_ROWS_WG), 0, s, c, a);
+    hipLaunchKernelGGL((k_ilu_skew<GAL, true>), sg, dim3(HH_ILU_PW), 0, s, c, a, tiles);
+}
+
 template <int DIM, typename T>
 static void vcycle_t(const Plan &pl, int fsel, int osel, const void *fptr, void *optr, hipStream_t s)
 {
@@ -1218,20 +1232,17 @@ static void vcycle_t(const Plan &pl, int fsel, int osel, const void *fptr, void 
                 // HH_ILU_INNER_MAX points (HH_ILU_FUSED: never)
                 const bool rows = !getenv("HH_ILU_GLOBAL"), gal = a.fl.g != nullptr;
                 const int nx = a.fl.n[0], ny = a.fl.n[1];
-                a.diag = rows ? 1 : 0;
                 a.chan = (uint64_t *)(a.fl.w + ilu_w_values(nx, ny, gal));
                 a.inner = !rows && (a.fl.N <= HH_ILU_INNER_MAX || getenv("HH_ILU_FUSED")) ? 1 : 0;
                 const dim3 pg((unsigned)((a.fl.N + HH_ILU_PW - 1) / HH_ILU_PW));
-                if (!a.inner) {
-                    hipLaunchKernelGGL(k_ilu_prolong, pg, dim3(HH_ILU_PW), 0, s, c, a);
-                    hipLaunchKernelGGL(k_ilu_resid, pg, dim3(HH_ILU_PW), 0, s, c, a);
+                if (!a.inner) hipLaunchKernelGGL(k_ilu_prolong, pg, dim3(HH_ILU_PW), 0, s, c, a);
+                if (rows) {
+                    if (gal) launch_ilu_rows<true>(c, a, s);
+                    else launch_ilu_rows<false>(c, a, s);
+                    continue;
                 }
-                if (rows && gal)
-                    hipLaunchKernelGGL(k_ilu_up_rows<true>, dim3(ilu_groups<true>(nx, ny)), dim3(HH_ILU_ROWS_WG), 0, s, c, a);
-                else if (rows)
-                    hipLaunchKernelGGL(k_ilu_up_rows<false>, dim3(ilu_groups<false>(nx, ny)), dim3(HH_ILU_ROWS_WG), 0, s, c, a);
-                else
-                    hipLaunchKernelGGL(k_ilu_up, dim3(1), dim3(HH_ILU_WG), 0, s, c, a);
+                if (!a.inner) hipLaunchKernelGGL(k_ilu_resid, pg, dim3(HH_ILU_PW), 0, s, c, a);
+                hipLaunchKernelGGL(k_ilu_up, dim3(1), dim3(HH_ILU_WG), 0, s, c, a);
                 if (!a.inner) hipLaunchKernelGGL(k_ilu_update, pg, dim3(HH_ILU_PW), 0, s, c, a);
             }
             return;
