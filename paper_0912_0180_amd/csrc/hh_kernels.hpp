@@ -2432,13 +2432,13 @@ __global__ __launch_bounds__(NT) void k_vdown_m(Ctx cx, LvChain<T, K> lc, const 
     constexpr int W0 = MD::width(0), N0 = W0 * W0, NL = (N0 + NT - 1) / NT;
     constexpr int W1 = MD::width(1), NQ = (W1 * W1 + NT - 1) / NT;
     constexpr int NF = MD::area(1, K + 1);      // f of levels 1 .. K
-    constexpr int NP = MD::area(1, K) + 1;      // phi of levels 1 .. K-1
+    constexpr int NP = MD::area(1, K);          // levels 1 .. K-1
     static_assert(K >= 2 && 2 * W0 <= NT, "one coefficient position per thread and level");
     __shared__ Cx U[N0];
     __shared__ Cx F0[N0];
-    __shared__ T PH0[N0];
+    __shared__ Cx D0[N0];                       // diagonals
     __shared__ Cx FK[NF];
-    __shared__ T PK[NP];
+    __shared__ Cx DK[NP], GK[NP];               // diagonals and Jacobi weights of levels 1 .. K-1
     __shared__ Cx CA[K][2 * W0], CC[K][2 * W0], CD[K][2 * W0];   // [k][axis * W_k + i]
 
     const Cx zero = cmk<T>(0, 0);
@@ -2493,19 +2493,6 @@ __global__ __launch_bounds__(NT) void k_vdown_m(Ctx cx, LvChain<T, K> lc, const 
             qd[k] = ldg(ax ? lc.L[k].d[1] : lc.L[k].d[0], g);
         }
     }
-    {
-        int off = 0;
-#pragma unroll
-        for (int k = 1; k < K; ++k) {
-            const int Wk = MD::width(k);
-#pragma unroll
-            for (int q = 0; q < NQ; ++q) {
-                const int l = tid + q * NT;
-                if (l < Wk * Wk) PK[off + l] = pk[k][q];
-            }
-            off += Wk * Wk;
-        }
-    }
 #pragma unroll
     for (int k = 0; k < K; ++k)
         if (tid < 2 * MD::width(k)) {
@@ -2515,7 +2502,8 @@ __global__ __launch_bounds__(NT) void k_vdown_m(Ctx cx, LvChain<T, K> lc, const 
         }
     if (run != PH_RUN) return;   // uniform over the workgroup
     __syncthreads();
-    // level lev0: u1 = g f on the region
+    // u1 = g f on level lev0's region, and the diagonals and weights of every
+    // level: the coarser levels' steps then wait for nothing but the residual
     {
         const int nx = lc.L[0].n[0], ny = lc.L[0].n[1];
 #pragma unroll
@@ -2524,46 +2512,49 @@ __global__ __launch_bounds__(NT) void k_vdown_m(Ctx cx, LvChain<T, K> lc, const 
             if (l >= N0) break;
             const int lx = l % W0, ly = l / W0;
             const int gx = mdown_origin<K>(cx0, 0) + lx, gy = mdown_origin<K>(cy0, 0) + ly;
-            Cx u1 = zero;
+            Cx u1 = zero, D = zero;
             if (gx >= 0 && gx < nx && gy >= 0 && gy < ny) {
                 Cx d = cadd<T>(CD[0][lx], CD[0][W0 + ly]);
-                Cx D = cmk<T>(d.x - pr[q], d.y);
-                T qq = jscale<T>(omega, D);
-                Cx gw = cmk<T>(D.x * qq, -(D.y * qq));
-                if (pre) u1 = cmul<T>(gw, fr[q]);
+                D = cmk<T>(d.x - pr[q], d.y);
+                if (pre) u1 = cmul<T>(jweight<T>(D, omega), fr[q]);
             }
             U[l] = u1;
             F0[l] = fr[q];
-            PH0[l] = pr[q];
+            D0[l] = D;
+        }
+        int off = 0;
+#pragma unroll
+        for (int k = 1; k < K; ++k) {
+            const int Wk = MD::width(k), nxk = lc.L[k].n[0], nyk = lc.L[k].n[1];
+#pragma unroll
+            for (int q = 0; q < NQ; ++q) {
+                const int l = tid + q * NT;
+                if (l >= Wk * Wk) break;
+                const int lx = l % Wk, ly = l / Wk;
+                const int gx = mdown_origin<K>(cx0, k) + lx, gy = mdown_origin<K>(cy0, k) + ly;
+                Cx D = zero, gw = zero;
+                if (gx >= 0 && gx < nxk && gy >= 0 && gy < nyk) {
+                    Cx d = cadd<T>(CD[k][lx], CD[k][Wk + ly]);
+                    D = cmk<T>(d.x - pk[k][q], d.y);
+                    gw = jweight<T>(D, omega);
+                }
+                DK[off + l] = D;
+                GK[off + l] = gw;
+            }
+            off += Wk * Wk;
         }
     }
     __syncthreads();
     const T w0 = (T)0.125, w1 = (T)0.375;
-    int foff = 0, poff = 0;   // level k's f and phi in FK / PK (k >= 1)
+    int foff = 0;   // level k's f, diagonals and weights in FK, DK, GK (k >= 1)
 #pragma unroll
     for (int k = 0; k < K; ++k) {
         const int Wk = MD::width(k), Wn = MD::width(k + 1);
         const int nx = lc.L[k].n[0], ny = lc.L[k].n[1];
         Cx *Fk = k == 0 ? F0 : FK + foff;
-        const T *Pk = k == 0 ? PH0 : PK + poff;
+        const Cx *Dk = k == 0 ? D0 : DK + foff;
         Cx *Fn = FK + (k == 0 ? 0 : foff + Wk * Wk);
-        if (k > 0) {
-            // u1 = g f on the region
-            for (int l = tid; l < Wk * Wk; l += NT) {
-                const int lx = l % Wk, ly = l / Wk;
-                const int gx = mdown_origin<K>(cx0, k) + lx, gy = mdown_origin<K>(cy0, k) + ly;
-                Cx u1 = zero;
-                if (gx >= 0 && gx < nx && gy >= 0 && gy < ny) {
-                    Cx d = cadd<T>(CD[k][lx], CD[k][Wk + ly]);
-                    Cx D = cmk<T>(d.x - Pk[l], d.y);
-                    T qq = jscale<T>(omega, D);
-                    Cx gw = cmk<T>(D.x * qq, -(D.y * qq));
-                    if (pre) u1 = cmul<T>(gw, Fk[l]);
-                }
-                U[l] = u1;
-            }
-            __syncthreads();
-        }
+        const Cx *Gn = GK + (k == 0 ? 0 : foff + Wk * Wk);
         // r = f - M u1 on the region minus its outer ring, in place
         for (int r = tid; r < (Wk - 2) * (Wk - 2); r += NT) {
             const int lx = 1 + r % (Wk - 2), ly = 1 + r / (Wk - 2);
@@ -2571,9 +2562,7 @@ __global__ __launch_bounds__(NT) void k_vdown_m(Ctx cx, LvChain<T, K> lc, const 
             const int l = lx + Wk * ly;
             Cx res = zero;
             if (gx >= 0 && gx < nx && gy >= 0 && gy < ny) {
-                Cx d = cadd<T>(CD[k][lx], CD[k][Wk + ly]);
-                Cx D = cmk<T>(d.x - Pk[l], d.y);
-                Cx mu = cmul<T>(D, U[l]);
+                Cx mu = cmul<T>(Dk[l], U[l]);
                 mu = cmsub<T>(mu, CA[k][lx], U[l - 1]);
                 mu = cmsub<T>(mu, CC[k][lx], U[l + 1]);
                 mu = cmsub<T>(mu, CA[k][Wk + ly], U[l - Wk]);
@@ -2583,8 +2572,8 @@ __global__ __launch_bounds__(NT) void k_vdown_m(Ctx cx, LvChain<T, K> lc, const 
             Fk[l] = res;
         }
         __syncthreads();
-        // full weighting onto level k + 1's region (zero outside the grid);
-        // the workgroup's own part goes to memory
+        // full weighting onto level k + 1's region (zero outside the grid) and
+        // u1 there; the workgroup's own part of f goes to memory
         {
             const int ncx = lc.L[k + 1].n[0], ncy = lc.L[k + 1].n[1];
             const int own = 2 * ((1 << (K - k - 1)) - 1), ownw = C << (K - k - 1);
@@ -2592,7 +2581,7 @@ __global__ __launch_bounds__(NT) void k_vdown_m(Ctx cx, LvChain<T, K> lc, const 
             for (int cl = tid; cl < Wn * Wn; cl += NT) {
                 const int ix = cl % Wn, iy = cl / Wn;
                 const int I = mdown_origin<K>(cx0, k + 1) + ix, J = mdown_origin<K>(cy0, k + 1) + iy;
-                Cx acc_y = zero;
+                Cx acc_y = zero, u1 = zero;
                 if (I >= 0 && I < ncx && J >= 0 && J < ncy) {
                     const int bxl = 2 * ix + 1, byl = 2 * iy + 1;
 #pragma unroll
@@ -2607,15 +2596,16 @@ __global__ __launch_bounds__(NT) void k_vdown_m(Ctx cx, LvChain<T, K> lc, const 
                     }
                     if (ix >= own && ix < own + ownw && iy >= own && iy < own + ownw)
                         stg(fout, I + (int64_t)ncx * J, acc_y);
+                    if (k + 1 < K && pre) u1 = cmul<T>(Gn[cl], acc_y);
                 }
-                Fn[cl] = acc_y;
+                if (k + 1 < K) {
+                    Fn[cl] = acc_y;
+                    U[cl] = u1;
+                }
             }
         }
-        __syncthreads();
-        if (k > 0) {
-            foff += Wk * Wk;
-            poff += Wk * Wk;
-        }
+        if (k + 1 < K) __syncthreads();
+        if (k > 0) foff += Wk * Wk;
     }
 }
 
@@ -2624,13 +2614,11 @@ __global__ __launch_bounds__(NT) void k_vup_m(Ctx cx, LvChain<T, K> lc, const vo
 {
     using Cx = V2<T>;
     using MU = MergeUp<K, UT>;
-    constexpr int RW0 = MU::rw(0), NR = MU::rarea(0, K), NE = MU::earea(1, K + 1), NPOS = MU::rpos(0, K);
+    constexpr int RW0 = MU::rw(0), NE = MU::earea(1, K + 1), NPOS = MU::rpos(0, K);
     constexpr int RQ = (RW0 * RW0 + NT - 1) / NT;   // loads per thread and level (level 0 is the largest)
     constexpr int WK = MU::width(K), EQ = (WK * WK + NT - 1) / NT;
     static_assert(K >= 2 && 2 * RW0 <= NT, "one coefficient position per thread and level");
     __shared__ Cx U[RW0 * RW0];
-    __shared__ Cx F[NR];
-    __shared__ T PH[NR];
     __shared__ Cx E[NE];                  // e of levels 1 .. K
     __shared__ Cx CA[NPOS], CC[NPOS], CD[NPOS];
 
@@ -2703,24 +2691,15 @@ __global__ __launch_bounds__(NT) void k_vup_m(Ctx cx, LvChain<T, K> lc, const vo
         }
     }
     {
-        int roff = 0, coff = 0;
+        int coff = 0;
 #pragma unroll
         for (int k = 0; k < K; ++k) {
             const int R = MU::rw(k);
-#pragma unroll
-            for (int q = 0; q < RQ; ++q) {
-                const int l = tid + q * NT;
-                if (l < R * R) {
-                    F[roff + l] = fr[k][q];
-                    PH[roff + l] = pr[k][q];
-                }
-            }
             if (tid < 2 * R) {
                 CA[coff + tid] = qa[k];
                 CC[coff + tid] = qc[k];
                 CD[coff + tid] = qd[k];
             }
-            roff += R * R;
             coff += 2 * R;
         }
         Cx *EK = E + MU::earea(1, K);
@@ -2732,67 +2711,79 @@ __global__ __launch_bounds__(NT) void k_vup_m(Ctx cx, LvChain<T, K> lc, const vo
     }
     if (run != PH_RUN) return;   // uniform over the workgroup
     __syncthreads();
+    // a thread keeps its points of every level: f, the diagonal and the weight
+    // stay in registers from here to the level's smoothing
+    Cx Dr[K][RQ], gr[K][RQ];
+#pragma unroll
+    for (int k = 0; k < K; ++k) {
+        const int R = MU::rw(k);
+        const Cx *Dk = CD + MU::rpos(0, k);
+#pragma unroll
+        for (int q = 0; q < RQ; ++q) {
+            const int l = tid + q * NT;
+            Dr[k][q] = gr[k][q] = zero;
+            if (l < R * R) {
+                const Cx d = cadd<T>(Dk[l % R], Dk[R + l / R]);
+                Dr[k][q] = cmk<T>(d.x - pr[k][q], d.y);
+                gr[k][q] = jweight<T>(Dr[k][q], omega);
+            }
+        }
+    }
     const T p3 = (T)0.75, p1 = (T)0.25;
 #pragma unroll
     for (int k = K - 1; k >= 0; --k) {
         const int R = MU::rw(k), WE = MU::width(k + 1), WO = MU::width(k);
-        const int roff = MU::rarea(0, k), coff = MU::rpos(0, k);
-        const Cx *Fk = F + roff;
-        const T *Pk = PH + roff;
-        const Cx *Ak = CA + coff, *Ck = CC + coff, *Dk = CD + coff;
+        const Cx *Ak = CA + MU::rpos(0, k), *Ck = CC + MU::rpos(0, k);
         const Cx *Ec = E + MU::earea(1, k + 1);   // e of level k + 1
         Cx *Eo = E + (k > 0 ? MU::earea(1, k) : 0);
         const int nx = lc.L[k].n[0], ny = lc.L[k].n[1];
         const int x0 = ox[k] - 1, y0 = oy[k] - 1;
         // u2 = g f + P e on the region with its halo
-        for (int l = tid; l < R * R; l += NT) {
+        Cx ur[RQ];
+#pragma unroll
+        for (int q = 0; q < RQ; ++q) {
+            const int l = tid + q * NT;
+            if (l >= R * R) break;
             const int lx = l % R, ly = l / R;
             const int gx = x0 + lx, gy = y0 + ly;
-            Cx u2 = zero;
+            ur[q] = zero;
             if (lx < wx[k] + 2 && ly < wy[k] + 2 && gx >= 0 && gx < nx && gy >= 0 && gy < ny) {
-                Cx d = cadd<T>(Dk[lx], Dk[R + ly]);
-                Cx D = cmk<T>(d.x - Pk[l], d.y);
-                T qq = jscale<T>(omega, D);
-                Cx gw = cmk<T>(D.x * qq, -(D.y * qq));
-                Cx u1 = pre ? cmul<T>(gw, Fk[l]) : zero;
+                const Cx u1 = pre ? cmul<T>(gr[k][q], fr[k][q]) : zero;
                 const int Ix = (gx >> 1) - ox[k + 1], Iox = ((gx & 1) ? (gx >> 1) + 1 : (gx >> 1) - 1) - ox[k + 1];
                 const int Iy = (gy >> 1) - oy[k + 1], Ioy = ((gy & 1) ? (gy >> 1) + 1 : (gy >> 1) - 1) - oy[k + 1];
                 Cx a0 = crs2<T>(p3, Ec[Ix + WE * Iy], p1, Ec[Iox + WE * Iy]);
                 Cx a1 = crs2<T>(p3, Ec[Ix + WE * Ioy], p1, Ec[Iox + WE * Ioy]);
-                Cx pe = crs2<T>(p3, a0, p1, a1);
-                u2 = cadd<T>(u1, pe);
+                ur[q] = cadd<T>(u1, crs2<T>(p3, a0, p1, a1));
             }
-            U[l] = u2;
+            U[l] = ur[q];
         }
         __syncthreads();
-        // post-smoothing on the region; level lev0's goes to memory
-        for (int r = tid; r < WO * WO; r += NT) {
-            const int ix = r % WO, iy = r / WO;
-            if (ix >= wx[k] || iy >= wy[k]) continue;
-            const int lx = ix + 1, ly = iy + 1;
+        // post-smoothing on the region (the points inside the halo); level
+        // lev0's goes to memory
+#pragma unroll
+        for (int q = 0; q < RQ; ++q) {
+            const int l = tid + q * NT;
+            if (l >= R * R) break;
+            const int lx = l % R, ly = l / R;
+            if (lx < 1 || ly < 1 || lx > wx[k] || ly > wy[k]) continue;
             const int gx = x0 + lx, gy = y0 + ly;
-            const int l = lx + R * ly;
             Cx u = zero;
             const bool in = gx >= 0 && gx < nx && gy >= 0 && gy < ny;
             if (in) {
-                Cx d = cadd<T>(Dk[lx], Dk[R + ly]);
-                Cx D = cmk<T>(d.x - Pk[l], d.y);
-                T qq = jscale<T>(omega, D);
-                Cx gw = cmk<T>(D.x * qq, -(D.y * qq));
-                Cx mu = cmul<T>(D, U[l]);
+                Cx mu = cmul<T>(Dr[k][q], ur[q]);
                 mu = cmsub<T>(mu, Ak[lx], U[l - 1]);
                 mu = cmsub<T>(mu, Ck[lx], U[l + 1]);
                 mu = cmsub<T>(mu, Ak[R + ly], U[l - R]);
                 mu = cmsub<T>(mu, Ck[R + ly], U[l + R]);
-                u = cmadd<T>(U[l], gw, csub<T>(Fk[l], mu));
+                u = cmadd<T>(ur[q], gr[k][q], csub<T>(fr[k][q], mu));
             }
             if (k == 0) {
                 if (in) stg((Cx *)e0, gx + (int64_t)nx * gy, u);
             } else {
-                Eo[ix + WO * iy] = u;
+                Eo[(lx - 1) + WO * (ly - 1)] = u;
             }
         }
-        __syncthreads();
+        if (k > 0) __syncthreads();
     }
 }
 
