@@ -3602,21 +3602,55 @@ __global__ __launch_bounds__(TailCap<T>::WG) void k_vtail(Ctx cx, const int *__r
     if (up) __syncthreads();   // uniform
     C *U = (C *)(lds + tab.uoff);
     const T w0 = (T)0.125, w1 = (T)0.375, p3 = (T)0.75, p1 = (T)0.25;
+    // the top level's points stay with their threads, with their index,
+    // diagonal, weight and f in registers: all waves work there, and the
+    // issue of their instructions is what the kernel takes
+    constexpr int FT = (TailCap<T>::N + TailCap<T>::WG - 1) / TailCap<T>::WG;
+    const TailPtr<T> Q0 = tail_ptr<DIM, T>(lds, tab, t0);
+    int ti[FT], tj[FT], tk[FT];
+    C tD[FT], tg[FT], tf[FT];
+    if (t0 < L - 1) {
+#pragma unroll
+        for (int q = 0; q < FT; ++q) {
+            const int p = tid + q * nth;
+            if (p < Q0.N) {
+                tail_ijk(Q0, p, ti[q], tj[q], tk[q]);
+                tD[q] = tail_diag<DIM, T>(Q0, ti[q], tj[q], tk[q], p);
+                tg[q] = jweight<T>(tD[q], omega);
+                tf[q] = Q0.F[p];
+            }
+        }
+    }
     // down-legs
     for (int l = t0; l < L - 1 && !up; ++l) {
         const TailPtr<T> Q = tail_ptr<DIM, T>(lds, tab, l);
         const TailPtr<T> R = tail_ptr<DIM, T>(lds, tab, l + 1);
-        for (int p = tid; p < Q.N; p += nth) {
-            int i, j, k;
-            tail_ijk(Q, p, i, j, k);
-            U[p] = pre ? cmul<T>(jweight<T>(tail_diag<DIM, T>(Q, i, j, k, p), omega), Q.F[p]) : zero;
+        if (l == t0) {
+#pragma unroll
+            for (int q = 0; q < FT; ++q)
+                if (tid + q * nth < Q0.N) U[tid + q * nth] = pre ? cmul<T>(tg[q], tf[q]) : zero;
+        } else {
+            for (int p = tid; p < Q.N; p += nth) {
+                int i, j, k;
+                tail_ijk(Q, p, i, j, k);
+                U[p] = pre ? cmul<T>(jweight<T>(tail_diag<DIM, T>(Q, i, j, k, p), omega), Q.F[p]) : zero;
+            }
         }
         __syncthreads();
-        for (int p = tid; p < Q.N; p += nth) {
-            int i, j, k;
-            tail_ijk(Q, p, i, j, k);
-            C D = tail_diag<DIM, T>(Q, i, j, k, p);
-            Q.E[p] = csub<T>(Q.F[p], tail_Mu<DIM, T>(Q, U, D, i, j, k, p));   // residual kept in E
+        // residual, kept in E
+        if (l == t0) {
+#pragma unroll
+            for (int q = 0; q < FT; ++q) {
+                const int p = tid + q * nth;
+                if (p < Q0.N) Q0.E[p] = csub<T>(tf[q], tail_Mu<DIM, T>(Q0, U, tD[q], ti[q], tj[q], tk[q], p));
+            }
+        } else {
+            for (int p = tid; p < Q.N; p += nth) {
+                int i, j, k;
+                tail_ijk(Q, p, i, j, k);
+                C D = tail_diag<DIM, T>(Q, i, j, k, p);
+                Q.E[p] = csub<T>(Q.F[p], tail_Mu<DIM, T>(Q, U, D, i, j, k, p));
+            }
         }
         __syncthreads();
         for (int p = tid; p < R.N; p += nth) {
@@ -3683,10 +3717,8 @@ __global__ __launch_bounds__(TailCap<T>::WG) void k_vtail(Ctx cx, const int *__r
     for (int l = L - 2; l >= t0; --l) {
         const TailPtr<T> Q = tail_ptr<DIM, T>(lds, tab, l);
         const TailPtr<T> R = tail_ptr<DIM, T>(lds, tab, l + 1);
-        for (int p = tid; p < Q.N; p += nth) {
-            int i, j, k;
-            tail_ijk(Q, p, i, j, k);
-            C u1 = pre ? cmul<T>(jweight<T>(tail_diag<DIM, T>(Q, i, j, k, p), omega), Q.F[p]) : zero;
+        // P e at (i, j, k)
+        auto prolong = [&](int i, int j, int k) -> C {
             const int Ix = i >> 1, Iox = (i & 1) ? Ix + 1 : Ix - 1;
             const int Iy = j >> 1, Ioy = (j & 1) ? Iy + 1 : Iy - 1;
             // coarse values outside the level are zero (read clamped, then masked)
@@ -3714,7 +3746,35 @@ __global__ __launch_bounds__(TailCap<T>::WG) void k_vtail(Ctx cx, const int *__r
                 }
                 pe = crs2<T>(p3, pz[0], p1, pz[1]);
             }
-            U[p] = cadd<T>(u1, pe);
+            return pe;
+        };
+        if (l == t0) {
+            // e of the top level goes to memory
+            C u[FT];
+#pragma unroll
+            for (int q = 0; q < FT; ++q) {
+                const int p = tid + q * nth;
+                if (p < Q0.N) {
+                    u[q] = cadd<T>(pre ? cmul<T>(tg[q], tf[q]) : zero, prolong(ti[q], tj[q], tk[q]));
+                    U[p] = u[q];
+                }
+            }
+            __syncthreads();
+#pragma unroll
+            for (int q = 0; q < FT; ++q) {
+                const int p = tid + q * nth;
+                if (p < Q0.N) {
+                    const C mu = tail_Mu<DIM, T>(Q0, U, tD[q], ti[q], tj[q], tk[q], p);
+                    stg(eg_top, p, cmadd<T>(u[q], tg[q], csub<T>(tf[q], mu)));
+                }
+            }
+            return;
+        }
+        for (int p = tid; p < Q.N; p += nth) {
+            int i, j, k;
+            tail_ijk(Q, p, i, j, k);
+            const C u1 = pre ? cmul<T>(jweight<T>(tail_diag<DIM, T>(Q, i, j, k, p), omega), Q.F[p]) : zero;
+            U[p] = cadd<T>(u1, prolong(i, j, k));
         }
         __syncthreads();
         for (int p = tid; p < Q.N; p += nth) {
@@ -3726,11 +3786,8 @@ __global__ __launch_bounds__(TailCap<T>::WG) void k_vtail(Ctx cx, const int *__r
         }
         __syncthreads();
     }
-    // write e at the top tail level
-    {
-        const TailPtr<T> Q = tail_ptr<DIM, T>(lds, tab, t0);
-        for (int p = tid; p < Q.N; p += nth) stg(eg_top, p, Q.E[p]);
-    }
+    // the tail's top level is the coarsest
+    for (int p = tid; p < Q0.N; p += nth) stg(eg_top, p, Q0.E[p]);
 }
 
 // Waves k_coarse gives one coarsest solve of n unknowns (rows per wave as in
