@@ -2358,7 +2358,8 @@ __global__ __launch_bounds__(HH_ILU_ROWS_WG, 1) void k_ilu_up_rows(Ctx cx, IluAr
 // tail's first level, or a coarsest level that k_coarse solves, lev0 + K), one
 // launch per leg instead of K.  On these small levels a launch costs its
 // latency, not its work.  f0, e0: level lev0's right-hand side (of type TF:
-// the cycle's input on level 0) and result.
+// the cycle's input on level 0) and result.  One problem's kernels get the
+// levels by value; a batch's read them from each problem's descriptors.
 //
 // Down: the smoothing from zero is pointwise, so a coarse point's restricted
 // residual depends only on the finer level within two points of its
@@ -2377,6 +2378,28 @@ __global__ __launch_bounds__(HH_ILU_ROWS_WG, 1) void k_ilu_up_rows(Ctx cx, IluAr
 template <typename T, int K> struct LvChain {
     LevelDev<T> L[K + 1];
 };
+// the last K + 1 levels of a batch's problem (its merged legs end at the
+// coarsest level); field by field, so that every load is a scalar one
+template <typename P> __device__ __forceinline__ P ldu(const P *p) { return *(const HH_GLOBAL P *)p; }
+template <typename T, int K> __device__ __forceinline__ LvChain<T, K> coarse_chain(const ProbDev *pd)
+{
+    const LevelDev<T> *Lv = levels<T>(pd) + (pd->nlev - 1 - K);
+    LvChain<T, K> lc;
+#pragma unroll
+    for (int k = 0; k <= K; ++k) {
+#pragma unroll
+        for (int a = 0; a < 2; ++a) {
+            lc.L[k].n[a] = ldu(&Lv[k].n[a]);
+            lc.L[k].a[a] = ldu(&Lv[k].a[a]);
+            lc.L[k].c[a] = ldu(&Lv[k].c[a]);
+            lc.L[k].d[a] = ldu(&Lv[k].d[a]);
+        }
+        lc.L[k].phi = ldu(&Lv[k].phi);
+        lc.L[k].f = ldu(&Lv[k].f);
+        lc.L[k].e = ldu(&Lv[k].e);
+    }
+    return lc;
+}
 // (no recursion: the sizes fold to constants once the level loops unroll)
 template <int K, int C> struct MergeDown {
     // W_K = C, W_k = 2 W_{k+1} + 4, for 0 <= k <= K
@@ -2424,8 +2447,9 @@ template <int K> __device__ __forceinline__ int mdown_origin(int c0, int k)
     return (c0 << (K - k)) - 2 * ((1 << (K - k)) - 1);
 }
 
+// b: the workgroup's tile; run: PH_RUN, checked once the loads are out
 template <typename T, typename TF, int K, int C, int NT>
-__global__ __launch_bounds__(NT) void k_vdown_m(Ctx cx, LvChain<T, K> lc, const void *f0)
+__device__ __forceinline__ void vdown_m(const LvChain<T, K> &lc, const void *f0, int b, int run, T omega, bool pre)
 {
     using Cx = V2<T>;
     using MD = MergeDown<K, C>;
@@ -2443,11 +2467,7 @@ __global__ __launch_bounds__(NT) void k_vdown_m(Ctx cx, LvChain<T, K> lc, const 
 
     const Cx zero = cmk<T>(0, 0);
     const int tid = threadIdx.x;
-    const int run = phase_of(cx, 0);
-    const T omega = (T)(cx.L ? cx.omega : cx.P->omega);
-    const bool pre = (cx.L ? cx.nu1 : cx.P->nu1) != 0;
     const int tx = (lc.L[K].n[0] + C - 1) / C;
-    const int b = tile_of(cx).idx;
     const int cx0 = (b % tx) * C, cy0 = (b / tx) * C;
     // all global loads first: f and phi of level lev0 on its region, phi of
     // levels 1 .. K-1 on theirs, the coefficients of levels 0 .. K-1
@@ -2610,7 +2630,7 @@ __global__ __launch_bounds__(NT) void k_vdown_m(Ctx cx, LvChain<T, K> lc, const 
 }
 
 template <typename T, typename TF, int K, int UT, int NT>
-__global__ __launch_bounds__(NT) void k_vup_m(Ctx cx, LvChain<T, K> lc, const void *f0, void *e0)
+__device__ __forceinline__ void vup_m(const LvChain<T, K> &lc, const void *f0, void *e0, int b, int run, T omega, bool pre)
 {
     using Cx = V2<T>;
     using MU = MergeUp<K, UT>;
@@ -2624,11 +2644,7 @@ __global__ __launch_bounds__(NT) void k_vup_m(Ctx cx, LvChain<T, K> lc, const vo
 
     const Cx zero = cmk<T>(0, 0);
     const int tid = threadIdx.x;
-    const int run = phase_of(cx, 0);
-    const T omega = (T)(cx.L ? cx.omega : cx.P->omega);
-    const bool pre = (cx.L ? cx.nu1 : cx.P->nu1) != 0;
     const int tx = (lc.L[0].n[0] + UT - 1) / UT;
-    const int b = tile_of(cx).idx;
     // e regions: level 0 is the tile; level k + 1's covers the prolongation
     // footprint of level k's region plus its halo of one
     int ox[K + 1], oy[K + 1], wx[K + 1], wy[K + 1];
@@ -2785,6 +2801,59 @@ __global__ __launch_bounds__(NT) void k_vup_m(Ctx cx, LvChain<T, K> lc, const vo
         }
         if (k > 0) __syncthreads();
     }
+}
+
+// one problem: the levels by value
+template <typename T, typename TF, int K, int C, int NT>
+__global__ __launch_bounds__(NT) void k_vdown_m(Ctx cx, LvChain<T, K> lc, const void *f0)
+{
+    vdown_m<T, TF, K, C, NT>(lc, f0, tile_of(cx).idx, phase_of(cx, 0), (T)(cx.L ? cx.omega : cx.P->omega),
+                             (cx.L ? cx.nu1 : cx.P->nu1) != 0);
+}
+template <typename T, typename TF, int K, int UT, int NT>
+__global__ __launch_bounds__(NT) void k_vup_m(Ctx cx, LvChain<T, K> lc, const void *f0, void *e0)
+{
+    vup_m<T, TF, K, UT, NT>(lc, f0, e0, tile_of(cx).idx, phase_of(cx, 0), (T)(cx.L ? cx.omega : cx.P->omega),
+                            (cx.L ? cx.nu1 : cx.P->nu1) != 0);
+}
+
+// a batch: each problem's own number of levels (batch_kdown, batch_kup), so
+// that all problems' merged legs are one launch
+__host__ __device__ inline int batch_kdown(int nlev) { return nlev - 2 < 3 ? nlev - 2 : 3; }
+__host__ __device__ inline int batch_kup(int nlev) { return nlev - 2 < 4 ? nlev - 2 : 4; }
+// edge of an up-leg's tile
+__host__ __device__ constexpr int batch_ut(int kup) { return kup == 4 ? 32 : 16; }
+template <typename T, int K, int C, int NT>
+__device__ __forceinline__ void batch_down(const ProbDev *pd, int b)
+{
+    const LvChain<T, K> lc = coarse_chain<T, K>(pd);
+    vdown_m<T, V2<T>, K, C, NT>(lc, lc.L[0].f, b, PH_RUN, (T)pd->omega, pd->nu1 != 0);
+}
+template <typename T, int K, int NT>
+__device__ __forceinline__ void batch_up(const ProbDev *pd, int b)
+{
+    const LvChain<T, K> lc = coarse_chain<T, K>(pd);
+    vup_m<T, V2<T>, K, batch_ut(K), NT>(lc, lc.L[0].f, lc.L[0].e, b, PH_RUN, (T)pd->omega, pd->nu1 != 0);
+}
+template <typename T, int C, int NT>
+__global__ __launch_bounds__(NT) void k_vdown_mb(Ctx cx)
+{
+    const Tile tl = tile_of(cx);
+    if (phase_of(cx, tl.prob) != PH_RUN) return;
+    const ProbDev *pd = cx.P + tl.prob;
+    if (batch_kdown(pd->nlev) == 3) batch_down<T, 3, C, NT>(pd, tl.idx);
+    else batch_down<T, 2, C, NT>(pd, tl.idx);
+}
+template <typename T, int NT>
+__global__ __launch_bounds__(NT) void k_vup_mb(Ctx cx)
+{
+    const Tile tl = tile_of(cx);
+    if (phase_of(cx, tl.prob) != PH_RUN) return;
+    const ProbDev *pd = cx.P + tl.prob;
+    const int K = batch_kup(pd->nlev);
+    if (K == 4) batch_up<T, 4, NT>(pd, tl.idx);
+    else if (K == 3) batch_up<T, 3, NT>(pd, tl.idx);
+    else batch_up<T, 2, NT>(pd, tl.idx);
 }
 
 // ---------------------------------------------------------------------------
@@ -3801,9 +3870,9 @@ template <typename T> __host__ __device__ inline int coarse_waves(int n)
 
 // Coarsest solve e = Minv f with the rows spread over workgroups: wave w of
 // the problem takes rows w, w + W, ... (W waves in all), each row summed
-// exactly as in the tail kernel.  f is staged in LDS.  SEG = coarse_seg(Nc)
-// of every problem in the launch.
-template <typename T, int SEG>
+// exactly as in the tail kernel.  f is staged in LDS.  One launch for all
+// problems of a batch, whatever their coarse_seg(Nc): the branch is uniform.
+template <typename T>
 __global__ __launch_bounds__(HH_WG) void k_coarse(Ctx cx)
 {
     using C = V2<T>;
@@ -3819,7 +3888,14 @@ __global__ __launch_bounds__(HH_WG) void k_coarse(Ctx cx)
     const C *__restrict__ Minv = (const C *)(sizeof(T) == 8 ? (const void *)pd->Minv64 : (const void *)pd->Minv32);
     const int w = tl.idx * (HH_WG / 64) + (int)(threadIdx.x >> 6), W = coarse_waves<T>(n);
     if (w >= W) return;
-    coarse_rows_seg<T, SEG>(Minv, fs, Lv[L - 1].e, n, w, W);
+    C *e = Lv[L - 1].e;
+    switch (coarse_seg(n)) {
+    case 1: coarse_rows_seg<T, 1>(Minv, fs, e, n, w, W); break;
+    case 2: coarse_rows_seg<T, 2>(Minv, fs, e, n, w, W); break;
+    case 4: coarse_rows_seg<T, 4>(Minv, fs, e, n, w, W); break;
+    case 8: coarse_rows_seg<T, 8>(Minv, fs, e, n, w, W); break;
+    default: coarse_rows_seg<T, 16>(Minv, fs, e, n, w, W);   // n <= HH_MAX_COARSE
+    }
 }
 
 // ---------------------------------------------------------------------------

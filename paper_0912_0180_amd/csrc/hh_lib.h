@@ -21,7 +21,7 @@ struct Plan {
     int count = 0, dim = 2, Lmax = 0;
     bool fp32 = false;
     DevList chunks, down[HH_MAXLEV], up[HH_MAXLEV];   // down/up: levels above the tail
-    DevList coarse[5];               // k_coarse workgroups of problems with a split tail, by log2(seg)
+    DevList coarse;                  // k_coarse workgroups
     bool tail_down = false;          // some problem needs the (full or down-only) tail kernel
     bool tail_up = false;            // some problem needs the up-only tail kernel
     int vdv[HH_MAXLEV] = {}, vuv[HH_MAXLEV] = {};   // tile shape of each level's down- and up-leg
@@ -29,8 +29,9 @@ struct Plan {
     // the tail) run as one merged launch of mdn workgroups, the up-legs of
     // levels mlev0u .. mlev0u + mKup - 1 (ending at the tail too) as one of mup
     int mK = 0, mlev0 = 0, mdn = 0, mKup = 0, mlev0u = 0, mup = 0;
-    int *fin = nullptr;
-    int nfin = 0;
+    DevList bdn, bup;                // a 2D batch: workgroups of its merged legs (see batch_merge)
+    int *fin = nullptr, *tail = nullptr;   // problems: all, those with a tail kernel
+    int nfin = 0, ntail = 0;
     ProbDev *probs = nullptr;
     Ctrl *ctrl = nullptr;            // per-problem control blocks (device)
     ProbDev pd1{};                   // one-problem plans: copy of the problem's static descriptor

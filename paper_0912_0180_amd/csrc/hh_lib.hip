@@ -393,8 +393,8 @@ static void grid_release(hh_grid *g)
 // over three levels: more workgroups than that cost more in redundant halo
 // work than they gain.  HH_MERGE=0 turns it off.
 template <typename T> struct MergeTile;
-template <> struct MergeTile<float> { static constexpr int C = 2, UT = 16, UT4 = 32, NT = 1024; };
-template <> struct MergeTile<double> { static constexpr int C = 2, UT = 16, UT4 = 32, NT = 1024; };
+template <> struct MergeTile<float> { static constexpr int C = 2, BC = 3, UT = 16, UT4 = 32, NT = 1024; };
+template <> struct MergeTile<double> { static constexpr int C = 2, BC = 2, UT = 16, UT4 = 32, NT = 1024; };
 
 // Level 0 takes part on grids of at most HH_MERGE_TOP points (its legs are then
 // latency too: 128^2 FP64 cycle 32 -> 21 us with the next rule), and where
@@ -432,6 +432,55 @@ static void plan_merge(Plan &pl, const hh_grid *const *G, int count, bool fp32)
     pl.mKup = Kup;
     pl.mlev0u = t - Kup;
     pl.mup = ceil_div(hs.lev[t - Kup].n[0], UT) * ceil_div(hs.lev[t - Kup].n[1], UT);
+}
+
+// Merged legs of a 2D batch: per problem the last two or three levels above the
+// coarsest (down) and the last two to four (up), k_coarse between them and no
+// tail kernel.  In a batch the levels below the finest ones are latency as in
+// a single cycle, and more of it: their launches follow the deepest problem,
+// and the tail kernel (one workgroup per problem) runs up to twice.  A problem
+// takes part if its last levels halve exactly and the merged ones lie below
+// level 0; the others keep the tiled legs and the tail.
+// Where the line lies, in us per Bi-CGSTAB iteration (two cycles) without and
+// with it, square problems with sides spread over the range given; "tiles":
+// 3 x 3 tiles of all coarsest grids:
+//   problems of             tiles  FP32 cycle    FP64 cycle
+//   2 of 128 .. 256            72   144 ->  120   109 ->   90
+//   2 of 256 .. 768            52   237 ->  203   208 ->  179
+//   8 of 128 .. 320           170   249 ->  214   184 ->  169
+//   8 of 256 .. 768           185   452 ->  410   380 ->  357
+//   16 of 256 .. 768          368   660 ->  660   608 ->  635
+//   32 of 256 .. 768          805  1166 -> 1231  1115 -> 1216
+//   8 of 128 .. 512, coarsest 8^2 .. 11^2: the tail kernel solves them all
+//                                   294 ->  294   195 ->  195
+// A workgroup takes a CU (LDS), so more tiles than CUs run one after another,
+// each with its halo's extra work; and a batch whose tail kernel solves every
+// coarsest grid (none over HH_SPLIT_NC) has one launch there already.
+// The down-legs take tiles of BC coarsest points: 12.4 us with 2, 8.0 with 3,
+// 9.2 with 4 for 8 of 256 .. 768 in FP32; 2 in FP64, where 3 would not fit LDS.
+#define HH_BMERGE_AREA 256
+static std::vector<int> batch_merge(const std::vector<const hh_grid *> &G)
+{
+    std::vector<int> on(G.size(), 0);
+    if (G.size() < 2) return on;
+    if (const char *e = getenv("HH_MERGE"))
+        if (atoi(e) == 0) return on;
+    int64_t area = 0;
+    bool any = false;   // some problem has its coarsest grid solved by k_coarse anyhow
+    for (size_t q = 0; q < G.size(); ++q) {
+        const HostSetup &hs = G[q]->hs;
+        const int c = hs.nlev - 1;
+        if (hs.dim != 2 || G[q]->host_only || batch_kdown(hs.nlev) < 2) continue;
+        bool exact = true;
+        for (int l = c - batch_kup(hs.nlev); l < c; ++l)
+            exact = exact && hs.lev[l].n[0] == 2 * hs.lev[l + 1].n[0] && hs.lev[l].n[1] == 2 * hs.lev[l + 1].n[1];
+        if (!exact) continue;
+        on[q] = 1;
+        any = any || coarse_split(hs);
+        area += (int64_t)ceil_div(hs.lev[c].n[0], 3) * ceil_div(hs.lev[c].n[1], 3);
+    }
+    if (!any || area > HH_BMERGE_AREA) on.assign(G.size(), 0);
+    return on;
 }
 
 // launch plans: tile lists of every pass for a set of problems
@@ -645,50 +694,73 @@ hh_status plan_build(Plan &pl, const std::vector<const hh_grid *> &G, bool fp32)
     pl.dim = G.empty() ? 2 : G[0]->hs.dim;
     pl.fp32 = fp32;
     pl.Lmax = 0;
-    std::vector<Tile> chunks, down[HH_MAXLEV], up[HH_MAXLEV], coarse[5];
-    std::vector<int> fin;
+    std::vector<Tile> chunks, down[HH_MAXLEV], up[HH_MAXLEV], coarse, bdn, bup;
+    std::vector<int> fin, tail;
     pl.tail_down = pl.tail_up = false;
     plan_merge(pl, G.data(), (int)G.size(), fp32);
+    const std::vector<int> bm = batch_merge(G);
+    // levels of problem q with tiled down- and up-legs
+    auto ntiled = [&](int q, int leg) {
+        const int c = G[q]->hs.nlev - 1;
+        if (bm[q]) return c - (leg == 0 ? batch_kdown(c + 1) : batch_kup(c + 1));
+        return plan_tail(G[q], (int)G.size(), fp32);
+    };
     // tile shape per level and leg, tuned on the largest problem having the level
     for (int l = 0; l < HH_MAXLEV; ++l) {
         pl.vdv[l] = pl.vuv[l] = 0;
         if (pl.mK && l >= pl.mlev0) continue;   // merged levels (mlev0u <= mlev0)
-        const hh_grid *rep = nullptr;
-        for (const hh_grid *g : G)
-            if (l < plan_tail(g, (int)G.size(), fp32) && (!rep || g->hs.lev[l].N > rep->hs.lev[l].N)) rep = g;
-        if (!rep || rep->host_only) continue;
-        pl.vdv[l] = tune_leg(rep, fp32, 0, l);
-        if (!pl.mK || l < pl.mlev0u) pl.vuv[l] = tune_leg(rep, fp32, 1, l);
+        for (int leg = 0; leg < 2; ++leg) {
+            if (leg == 1 && pl.mK && l >= pl.mlev0u) continue;
+            const hh_grid *rep = nullptr;
+            for (int q = 0; q < pl.count; ++q)
+                if (l < ntiled(q, leg) && (!rep || G[q]->hs.lev[l].N > rep->hs.lev[l].N)) rep = G[q];
+            if (rep && !rep->host_only) (leg == 0 ? pl.vdv : pl.vuv)[l] = tune_leg(rep, fp32, leg, l);
+        }
     }
     for (int q = 0; q < pl.count; ++q) {
         const HostSetup &hs = G[q]->hs;
-        const int t = plan_tail(G[q], pl.count, fp32);
-        pl.Lmax = std::max(pl.Lmax, t);
+        const int t = plan_tail(G[q], pl.count, fp32), c = hs.nlev - 1;
         const bool split = coarse_split(hs);
-        if (split) {
+        pl.Lmax = std::max(pl.Lmax, std::max(ntiled(q, 0), ntiled(q, 1)));
+        if (split || bm[q]) {
             const int nwg = ceil_div(fp32 ? coarse_waves<float>(hs.Nc) : coarse_waves<double>(hs.Nc), HH_WG / 64);
-            int lg = 0;
-            while ((1 << lg) < coarse_seg(hs.Nc)) ++lg;
-            for (int i = 0; i < nwg; ++i) coarse[lg].push_back(Tile{q, i});
+            for (int i = 0; i < nwg; ++i) coarse.push_back(Tile{q, i});
         }
-        if (!split || t < hs.nlev - 1) pl.tail_down = true;
-        if (split && t < hs.nlev - 1) pl.tail_up = true;
+        if (bm[q]) {
+            const int Kup = batch_kup(hs.nlev), UT = batch_ut(Kup);
+            const HostLevel &Lu = hs.lev[c - Kup];
+            const int C = fp32 ? MergeTile<float>::BC : MergeTile<double>::BC;
+            const int nd = ceil_div(hs.lev[c].n[0], C) * ceil_div(hs.lev[c].n[1], C);
+            const int nu = ceil_div(Lu.n[0], UT) * ceil_div(Lu.n[1], UT);
+            for (int i = 0; i < nd; ++i) bdn.push_back(Tile{q, i});
+            for (int i = 0; i < nu; ++i) bup.push_back(Tile{q, i});
+        } else {
+            if (!split || t < c) {
+                pl.tail_down = true;
+                tail.push_back(q);
+            }
+            if (split && t < c) pl.tail_up = true;
+        }
         const int ngr = ceil_div(hs.lev[0].N, HH_SPAN);
         for (int i = 0; i < ngr; ++i) chunks.push_back(Tile{q, i});
-        for (int l = 0; l < t; ++l) {
+        for (int l = 0; l < HH_MAXLEV; ++l) {
             int nd, nu;
-            vtile_counts(hs.dim, pl.vdv[l], hs.lev[l], hs.lev[l + 1], nd, nu);
-            for (int i = 0; i < nd; ++i) down[l].push_back(Tile{q, i});
-            vtile_counts(hs.dim, pl.vuv[l], hs.lev[l], hs.lev[l + 1], nd, nu);
-            for (int i = 0; i < nu; ++i) up[l].push_back(Tile{q, i});
+            if (l < ntiled(q, 0)) {
+                vtile_counts(hs.dim, pl.vdv[l], hs.lev[l], hs.lev[l + 1], nd, nu);
+                for (int i = 0; i < nd; ++i) down[l].push_back(Tile{q, i});
+            }
+            if (l < ntiled(q, 1)) {
+                vtile_counts(hs.dim, pl.vuv[l], hs.lev[l], hs.lev[l + 1], nd, nu);
+                for (int i = 0; i < nu; ++i) up[l].push_back(Tile{q, i});
+            }
         }
         fin.push_back(q);
     }
-    size_t bytes = align256(sizeof(Tile) * chunks.size()) +
-                   align256(sizeof(int) * fin.size()) +
+    size_t bytes = align256(sizeof(Tile) * chunks.size()) + align256(sizeof(Tile) * coarse.size()) +
+                   align256(sizeof(Tile) * bdn.size()) + align256(sizeof(Tile) * bup.size()) +
+                   align256(sizeof(int) * fin.size()) + align256(sizeof(int) * tail.size()) +
                    align256(sizeof(ProbDev) * pl.count) + align256(sizeof(Ctrl) * pl.count);
     for (int l = 0; l < HH_MAXLEV; ++l) bytes += align256(sizeof(Tile) * down[l].size()) + align256(sizeof(Tile) * up[l].size());
-    for (int g = 0; g < 5; ++g) bytes += align256(sizeof(Tile) * coarse[g].size());
     hipError_t e = hipMalloc(&pl.mem, bytes);
     if (e != hipSuccess) return hh_fail(HH_ERR_OOM, "hipMalloc(%zu) for a launch plan: %s", bytes, hipGetErrorString(e));
     pl.bytes = bytes;
@@ -700,7 +772,9 @@ hh_status plan_build(Plan &pl, const std::vector<const hh_grid *> &G, bool fp32)
         return v.empty() ? hipSuccess : hipMemcpy(d.t, v.data(), sizeof(Tile) * v.size(), hipMemcpyHostToDevice);
     };
     HIPCHK(up_list(chunks, pl.chunks));
-    for (int g = 0; g < 5; ++g) HIPCHK(up_list(coarse[g], pl.coarse[g]));
+    HIPCHK(up_list(coarse, pl.coarse));
+    HIPCHK(up_list(bdn, pl.bdn));
+    HIPCHK(up_list(bup, pl.bup));
     for (int l = 0; l < HH_MAXLEV; ++l) {
         HIPCHK(up_list(down[l], pl.down[l]));
         HIPCHK(up_list(up[l], pl.up[l]));
@@ -708,6 +782,9 @@ hh_status plan_build(Plan &pl, const std::vector<const hh_grid *> &G, bool fp32)
     pl.fin = c.take<int>(fin.size());
     pl.nfin = (int)fin.size();
     HIPCHK(hipMemcpy(pl.fin, fin.data(), sizeof(int) * fin.size(), hipMemcpyHostToDevice));
+    pl.tail = c.take<int>(tail.size());
+    pl.ntail = (int)tail.size();
+    if (pl.ntail) HIPCHK(hipMemcpy(pl.tail, tail.data(), sizeof(int) * tail.size(), hipMemcpyHostToDevice));
     pl.probs = c.take<ProbDev>(pl.count);
     pl.ctrl = c.take<Ctrl>(pl.count);
     if (pl.count == 1) {
@@ -1036,17 +1113,15 @@ static void plan_host_one(Plan &pl, const hh_grid *g, bool fp32, const void *L1,
         vtile_counts(hs.dim, pl.vuv[l], hs.lev[l], hs.lev[l + 1], nd, nu);
         pl.up[l].n = nu;
     }
-    for (int q = 0; q < 5; ++q) pl.coarse[q].n = 0;
+    pl.coarse.n = 0;
     const bool split = coarse_split(hs);
     if (split) {
-        int lg = 0;
-        while ((1 << lg) < coarse_seg(hs.Nc)) ++lg;
-        pl.coarse[lg].n = ceil_div(fp32 ? coarse_waves<float>(hs.Nc) : coarse_waves<double>(hs.Nc), HH_WG / 64);
+        pl.coarse.n = ceil_div(fp32 ? coarse_waves<float>(hs.Nc) : coarse_waves<double>(hs.Nc), HH_WG / 64);
     }
     pl.tail_down = !split || t < hs.nlev - 1;
     pl.tail_up = split && t < hs.nlev - 1;
     pl.chunks.n = ceil_div(hs.lev[0].N, HH_SPAN);
-    pl.nfin = 1;
+    pl.nfin = pl.ntail = 1;
     pl.probs = g->pd_static_dev;
     pl.ctrl = nullptr;
     pl.pd1 = g->pd_static;
@@ -1092,6 +1167,16 @@ static void launch_merged(int leg, const Plan &pl, hipStream_t s, const LvHost &
     const LevelDev<T> *L = lv_of<T>(lh);
     if ((leg == 0 ? pl.mlev0 : pl.mlev0u) == 0) launch_merged_t<T, double2>(leg, pl, s, L, fptr, optr);
     else launch_merged_t<T, V2<T>>(leg, pl, s, L, fptr, optr);
+}
+
+// the merged down- (leg 0) or up-legs (leg 1) of a 2D batch
+template <typename T> static void launch_batch_merged(int leg, const Plan &pl, hipStream_t s)
+{
+    constexpr int NT = MergeTile<T>::NT;
+    const DevList &d = leg == 0 ? pl.bdn : pl.bup;
+    if (d.n == 0) return;
+    if (leg == 0) hipLaunchKernelGGL((k_vdown_mb<T, MergeTile<T>::BC, NT>), dim3(d.n), dim3(NT), 0, s, ctx_of(pl, d));
+    else hipLaunchKernelGGL((k_vup_mb<T, NT>), dim3(d.n), dim3(NT), 0, s, ctx_of(pl, d));
 }
 
 // the fused legs of Galerkin level l >= 1 of a one-problem 2D plan (leg 0
@@ -1191,29 +1276,27 @@ static void vcycle_t(const Plan &pl, int fsel, int osel, const void *fptr, void 
         else launch_leg<DIM, T>(0, pl.vdv[l], pl.down[l].n, s, ctx_of(pl, pl.down[l]), l, fsel, osel, fptr, optr, lh);
     }
     if (pl.mK) launch_merged<T>(0, pl, s, lh, fptr, optr);
+    if constexpr (DIM == 2) launch_batch_merged<T>(0, pl, s);
     {
         // coarse part: tail kernel (whole, or down-legs of split problems),
         // multi-workgroup coarsest solves, up-legs of split problems
         Ctx c = ctx_of(pl, pl.chunks);
-        const int *probs = pl.count == 1 ? nullptr : pl.fin;
-        if (pl.nfin > 0 && pl.tail_down) {
+        const int *probs = pl.count == 1 ? nullptr : pl.tail;
+        if (pl.ntail > 0 && pl.tail_down) {
             if (pl.count == 1)
                 hipLaunchKernelGGL((k_vtail<DIM, T, true>), dim3(1), dim3(TailCap<T>::WG), 0, s, c, nullptr, 0, tail_args<T>(pl));
             else
-                hipLaunchKernelGGL((k_vtail<DIM, T, false>), dim3(pl.nfin), dim3(TailCap<T>::WG), 0, s, c, probs, 0, TailArgs<T>{});
+                hipLaunchKernelGGL((k_vtail<DIM, T, false>), dim3(pl.ntail), dim3(TailCap<T>::WG), 0, s, c, probs, 0, TailArgs<T>{});
         }
-        LAUNCH((k_coarse<T, 1>), pl.coarse[0].n, s, ctx_of(pl, pl.coarse[0]));
-        LAUNCH((k_coarse<T, 2>), pl.coarse[1].n, s, ctx_of(pl, pl.coarse[1]));
-        LAUNCH((k_coarse<T, 4>), pl.coarse[2].n, s, ctx_of(pl, pl.coarse[2]));
-        LAUNCH((k_coarse<T, 8>), pl.coarse[3].n, s, ctx_of(pl, pl.coarse[3]));
-        LAUNCH((k_coarse<T, 16>), pl.coarse[4].n, s, ctx_of(pl, pl.coarse[4]));
-        if (pl.nfin > 0 && pl.tail_up) {
+        LAUNCH((k_coarse<T>), pl.coarse.n, s, ctx_of(pl, pl.coarse));
+        if (pl.ntail > 0 && pl.tail_up) {
             if (pl.count == 1)
                 hipLaunchKernelGGL((k_vtail<DIM, T, true>), dim3(1), dim3(TailCap<T>::WG), 0, s, c, nullptr, 1, tail_args<T>(pl));
             else
-                hipLaunchKernelGGL((k_vtail<DIM, T, false>), dim3(pl.nfin), dim3(TailCap<T>::WG), 0, s, c, probs, 1, TailArgs<T>{});
+                hipLaunchKernelGGL((k_vtail<DIM, T, false>), dim3(pl.ntail), dim3(TailCap<T>::WG), 0, s, c, probs, 1, TailArgs<T>{});
         }
     }
+    if constexpr (DIM == 2) launch_batch_merged<T>(1, pl, s);
     if (pl.mK) launch_merged<T>(1, pl, s, lh, fptr, optr);
     if constexpr (DIM == 2 && std::is_same<T, double>::value) {
         if (pl.ilu) {
