@@ -1741,15 +1741,16 @@ struct IluArgs {
 // the neighbour outside the grid taken as zero: the Galerkin stencil, or the
 // 5-point set of the rediscretised stencil; y = M u in the contract's order
 // (reads clamped to the grid and masked, so that they issue together: a
-// branch per entry made 25 round trips of them)
-template <bool GAL> __device__ __forceinline__ double2 ilu_Mu(const LevelDev<double> &L, const double2 *u, int i, int j, int64_t p)
+// branch per entry made 25 round trips of them; UN entries at a time, as many
+// as the kernel has registers for)
+template <bool GAL, int UN = 25> __device__ __forceinline__ double2 ilu_Mu(const LevelDev<double> &L, const double2 *u, int i, int j, int64_t p)
 {
     const int nx = L.n[0], ny = L.n[1];
     const double2 zero = cmk<double>(0.0, 0.0);
     if (GAL) {
         const int64_t N = L.N;
         double2 t = cmul<double>(ldg(L.g, 12 * N + p), ldg(u, p));
-#pragma unroll
+#pragma unroll UN
         for (int s = 0; s < 25; ++s) {
             if (s == 12) continue;
             const int ii = i + s % 5 - 2, jj = j + s / 5 - 2;
@@ -1848,7 +1849,7 @@ __device__ __forceinline__ void ilu_resid_at(const IluArgs &a, int64_t p)
 {
     const int nx = a.fl.n[0];
     const int j = (int)fdiv((uint32_t)p, a.fl.fx), i = (int)p - j * nx;
-    stg(a.fl.w, p, csub<double>(ldg(a.f, p), a.fl.g ? ilu_Mu<true>(a.fl, a.u, i, j, p) : ilu_Mu<false>(a.fl, a.u, i, j, p)));
+    stg(a.fl.w, p, csub<double>(ldg(a.f, p), a.fl.g ? ilu_Mu<true, 4>(a.fl, a.u, i, j, p) : ilu_Mu<false>(a.fl, a.u, i, j, p)));
 }
 __device__ __forceinline__ void ilu_update_at(const IluArgs &a, int64_t p)
 {
