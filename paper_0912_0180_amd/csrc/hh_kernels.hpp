@@ -2019,11 +2019,12 @@ __global__ __launch_bounds__(HH_ILU_WG) void k_ilu_up(Ctx cx, IluArgs a)
 //     per row.  A row needs one new value per row above and step (column i + 2
 //     resp. i); the rest of its 5-column windows stay in registers.  New
 //     values pass from row to row through an LDS ring of 3 chunks of steps;
-//   * the feeding waves stream the chunk after next's factors and right-hand
-//     side into registers three chunks ahead and write them to the other of
-//     two LDS buffers; one of them also waits for the channel of the stage
-//     before and puts its values into the ring as rows -1 and -2, another
-//     publishes this stage's last rows;
+//   * the feeding waves load the factors and right-hand side of later chunks
+//     into registers and write them to the next of three LDS buffers, so the
+//     solving wave can read its first step of a chunk ahead of the barrier;
+//     one of them also waits for the channel of the stage before and puts its
+//     values into the ring as rows -1 and -2, another publishes this stage's
+//     last rows;
 //   * one barrier per chunk.
 // Channel words carry 32 bits of data and the launch's number (epoch), stored
 // and loaded as relaxed 64-bit atomics at device scope: a word with the
@@ -2031,8 +2032,10 @@ __global__ __launch_bounds__(HH_ILU_WG) void k_ilu_up(Ctx cx, IluArgs a)
 // Bound: the dependent steps, n_x + about 1.3 m n_y per solve, each about the
 // issue time of one wave's instructions.  One workgroup per level took 0.8-1.2
 // us per step (every row's loads, a barrier and the neighbour reads); as a
-// pipeline a 25-point step takes about 0.3 us, a 5-point one 0.16.  ILU(0)
-// V-cycle, 384^2: 3.46 -> 1.49 ms; 1280^2: 17.0 -> 5.1 ms.
+// pipeline a 25-point step takes about 500 cycles forward and 600 backward (a
+// complex division), a 5-point one 220 and 400: 0.2-0.25 us and 0.1-0.17 us.
+// ILU(0) V-cycle with the residual and update through LDS tiles (k_ilu_skew),
+// 384^2: 3.48 -> 1.09 ms; 1280^2: 17.0 -> 3.95 ms.
 // Values and operation order are k_ilu_up's: a product f q is taken as
 // (f.x a + f.y b) with (a, b) = (q.x, -q.y) resp. (q.y, q.x), which rounds as
 // cmul does; values outside the grid are +0 and their factors +0.
@@ -3871,9 +3874,11 @@ template <typename T> __host__ __device__ inline int coarse_waves(int n)
 
 // Coarsest solve e = Minv f with the rows spread over workgroups: wave w of
 // the problem takes rows w, w + W, ... (W waves in all), each row summed
-// exactly as in the tail kernel.  f is staged in LDS.  One launch for all
-// problems of a batch, whatever their coarse_seg(Nc): the branch is uniform.
-template <typename T>
+// exactly as in the tail kernel.  f is staged in LDS.  SEG = coarse_seg(Nc) of
+// a single problem; 0: one launch for all problems of a batch, whatever theirs
+// (a uniform branch; 4.8 us where two launches took 9.6, but the code of all
+// five forms costs a single cycle about 0.5 us).
+template <typename T, int SEG>
 __global__ __launch_bounds__(HH_WG) void k_coarse(Ctx cx)
 {
     using C = V2<T>;
@@ -3890,6 +3895,10 @@ __global__ __launch_bounds__(HH_WG) void k_coarse(Ctx cx)
     const int w = tl.idx * (HH_WG / 64) + (int)(threadIdx.x >> 6), W = coarse_waves<T>(n);
     if (w >= W) return;
     C *e = Lv[L - 1].e;
+    if constexpr (SEG > 0) {
+        coarse_rows_seg<T, SEG>(Minv, fs, e, n, w, W);
+        return;
+    }
     switch (coarse_seg(n)) {
     case 1: coarse_rows_seg<T, 1>(Minv, fs, e, n, w, W); break;
     case 2: coarse_rows_seg<T, 2>(Minv, fs, e, n, w, W); break;

@@ -382,7 +382,7 @@ static void grid_release(hh_grid *g)
 }
 
 // ---------------------------------------------------------------------------
-// Merged coarse legs (one 2D problem), each level exactly twice the next: the
+// Merged coarse legs (one 2D problem; batches: batch_merge), each level exactly twice the next: the
 // down-legs of the last K = 2 or 3 levels above the tail run as one launch,
 // the up-legs of the last 2 to 4 (their regions stay small) as another.
 // Down: C x C tiles of the tail's first level.  Up: UT x UT tiles of the
@@ -397,7 +397,7 @@ template <> struct MergeTile<float> { static constexpr int C = 2, BC = 3, UT = 1
 template <> struct MergeTile<double> { static constexpr int C = 2, BC = 2, UT = 16, UT4 = 32, NT = 1024; };
 
 // Level 0 takes part on grids of at most HH_MERGE_TOP points (its legs are then
-// latency too: 128^2 FP64 cycle 32 -> 21 us with the next rule), and where
+// latency too: 128^2 FP64 cycle 32 -> 18 us with the next rule), and where
 // k_coarse solves the coarsest level the merged legs end there: the tail
 // kernel's two launches beside it cost more than two more merged levels.
 #define HH_MERGE_TOP 65536
@@ -1288,7 +1288,14 @@ static void vcycle_t(const Plan &pl, int fsel, int osel, const void *fptr, void 
             else
                 hipLaunchKernelGGL((k_vtail<DIM, T, false>), dim3(pl.ntail), dim3(TailCap<T>::WG), 0, s, c, probs, 0, TailArgs<T>{});
         }
-        LAUNCH((k_coarse<T>), pl.coarse.n, s, ctx_of(pl, pl.coarse));
+        switch (pl.count == 1 ? coarse_seg(pl.pd1.Nc) : 0) {
+        case 0: LAUNCH((k_coarse<T, 0>), pl.coarse.n, s, ctx_of(pl, pl.coarse)); break;
+        case 1: LAUNCH((k_coarse<T, 1>), pl.coarse.n, s, ctx_of(pl, pl.coarse)); break;
+        case 2: LAUNCH((k_coarse<T, 2>), pl.coarse.n, s, ctx_of(pl, pl.coarse)); break;
+        case 4: LAUNCH((k_coarse<T, 4>), pl.coarse.n, s, ctx_of(pl, pl.coarse)); break;
+        case 8: LAUNCH((k_coarse<T, 8>), pl.coarse.n, s, ctx_of(pl, pl.coarse)); break;
+        default: LAUNCH((k_coarse<T, 16>), pl.coarse.n, s, ctx_of(pl, pl.coarse));
+        }
         if (pl.ntail > 0 && pl.tail_up) {
             if (pl.count == 1)
                 hipLaunchKernelGGL((k_vtail<DIM, T, true>), dim3(1), dim3(TailCap<T>::WG), 0, s, c, nullptr, 1, tail_args<T>(pl));
