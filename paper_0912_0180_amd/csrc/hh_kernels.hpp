@@ -2033,7 +2033,8 @@ __global__ __launch_bounds__(HH_ILU_WG) void k_ilu_up(Ctx cx, IluArgs a)
 // issue time of one wave's instructions.  One workgroup per level took 0.8-1.2
 // us per step (every row's loads, a barrier and the neighbour reads); as a
 // pipeline a 25-point step takes about 500 cycles forward and 600 backward (a
-// complex division), a 5-point one 220 and 400: 0.2-0.25 us and 0.1-0.17 us.
+// complex division), a 5-point one 220 and 400: 0.26 and 0.18 us on average,
+// the stages' lag included.
 // ILU(0) V-cycle with the residual and update through LDS tiles (k_ilu_skew),
 // 384^2: 3.48 -> 1.09 ms; 1280^2: 17.0 -> 3.95 ms.
 // Values and operation order are k_ilu_up's: a product f q is taken as
