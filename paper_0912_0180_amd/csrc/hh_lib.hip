@@ -1706,8 +1706,10 @@ hh_status hh_vcycle_noalloc(const hh_grid *g, hh_prec prec, const void *f, void 
 
 // Times the grid's V-cycle and its finest level's fused legs with HIP events
 // on `stream`: `reps` back-to-back cycles, then `reps` back-to-back launches of
-// the finest down-leg and of the finest up-leg, each leg exactly as the cycle
-// (and a solve's plan) launches it.
+// the finest down-leg and of the finest up-leg, each exactly as the cycle (and
+// a solve's plan) launches it: where the cycle merges the finest leg with the
+// next levels', the merged launch is the one timed.  Every leg reads what the
+// cycles before it left, and the last event is the call's last work.
 hh_status hh_profile_vcycle(const hh_grid *g, hh_prec prec, const void *f, void *u, int32_t reps,
                             hh_vcycle_profile *out, void *stream)
 {
@@ -1737,26 +1739,26 @@ hh_status hh_profile_vcycle(const hh_grid *g, hh_prec prec, const void *f, void 
     lh.d = pl.lv64h;
     lh.f = pl.lv32h;
     const Ctx cd = ctx_of(pl, pl.down[0]), cu = ctx_of(pl, pl.up[0]);
-    // the finest legs as launches of their own, also where the cycle merges
-    // them with the next levels'
-    const bool md = pl.mK && pl.mlev0 == 0, mu = pl.mK && pl.mlev0u == 0;
-    const int vd = md ? tune_leg(g, fp32, 0, 0) : pl.vdv[0], vu = mu ? tune_leg(g, fp32, 1, 0) : pl.vuv[0];
-    int nd = pl.down[0].n, nu = pl.up[0].n, other;
-    if (md) vtile_counts(g->hs.dim, vd, g->hs.lev[0], g->hs.lev[1], nd, other);
-    if (mu) vtile_counts(g->hs.dim, vu, g->hs.lev[0], g->hs.lev[1], other, nu);
-    launch_vcycle(pl, VS_IN, VS_OUT, f, u, s);   // warm-up
+    const bool merged[2] = {pl.mK && pl.mlev0 == 0, pl.mK && pl.mlev0u == 0};
+    auto finest = [&](int leg) {
+        if (!merged[leg])
+            launch_leg_any(g->hs.dim, fp32, leg, (leg == 0 ? pl.vdv : pl.vuv)[0], (leg == 0 ? pl.down : pl.up)[0].n, s,
+                           leg == 0 ? cd : cu, 0, VS_IN, VS_OUT, f, u, lh);
+        else if (fp32)
+            launch_merged<float>(leg, pl, s, lh, f, u);
+        else
+            launch_merged<double>(leg, pl, s, lh, f, u);
+    };
+    launch_vcycle(pl, VS_IN, VS_OUT, f, u, s);   // warm-up; leaves the f and e that the legs read valid
     hipError_t e = hipEventRecord(ev[0], s);
     for (int r = 0; r < reps; ++r) launch_vcycle(pl, VS_IN, VS_OUT, f, u, s);
     if (e == hipSuccess) e = hipEventRecord(ev[1], s);
     if (e == hipSuccess) e = hipEventRecord(ev[2], s);
-    for (int r = 0; r < reps; ++r)
-        launch_leg_any(g->hs.dim, fp32, 0, vd, nd, s, cd, 0, VS_IN, VS_OUT, f, u, lh);
+    for (int r = 0; r < reps; ++r) finest(0);
     if (e == hipSuccess) e = hipEventRecord(ev[3], s);
     if (e == hipSuccess) e = hipEventRecord(ev[4], s);
-    for (int r = 0; r < reps; ++r)
-        launch_leg_any(g->hs.dim, fp32, 1, vu, nu, s, cu, 0, VS_IN, VS_OUT, f, u, lh);
+    for (int r = 0; r < reps; ++r) finest(1);
     if (e == hipSuccess) e = hipEventRecord(ev[5], s);
-    if (mu) launch_vcycle(pl, VS_IN, VS_OUT, f, u, s);   // u = V(f) (merged legs leave no e on level 1)
     if (e == hipSuccess) e = hipGetLastError();
     if (e == hipSuccess) e = hipEventSynchronize(ev[5]);
     float ms[3] = {0.f, 0.f, 0.f};
@@ -1766,10 +1768,10 @@ hh_status hh_profile_vcycle(const hh_grid *g, hh_prec prec, const void *f, void 
     out->vcycle_us = 1e3 * ms[0] / reps;
     out->down_us = 1e3 * ms[1] / reps;
     out->up_us = 1e3 * ms[2] / reps;
-    out->down_shape = vd;
-    out->up_shape = vu;
-    out->down_groups = nd;
-    out->up_groups = nu;
+    out->down_shape = merged[0] ? -1 : pl.vdv[0];
+    out->up_shape = merged[1] ? -1 : pl.vuv[0];
+    out->down_groups = merged[0] ? pl.mdn : pl.down[0].n;
+    out->up_groups = merged[1] ? pl.mup : pl.up[0].n;
     return HH_OK;
 }
 

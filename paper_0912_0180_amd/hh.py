@@ -329,7 +329,8 @@ class Grid:
 
     def profile_vcycle(self, f, prec="c64", reps=50, out=None):
         """hh_profile_vcycle: average microseconds of one V-cycle and of one
-        launch of the finest level's down- and up-leg kernels."""
+        launch of the finest level's down- and up-leg kernels (shape -1: of
+        the merged kernel that holds the leg)."""
         torch = _torch()
         _need(f, torch.complex128, self.N, "f")
         dt = torch.complex128 if prec == "c128" else torch.complex64
