@@ -992,15 +992,19 @@ static int tune_leg(const hh_grid *g, bool fp32, int leg, int l)
         auto it = g_tune.find(key);
         if (it != g_tune.end()) return it->second;
     }
-    // time every shape on this grid's level (inputs of level 0 from a
-    // scratch buffer; the level arrays it writes are rewritten by every use).
+    // time every shape on this grid's level, with f and e of the two levels
+    // (and the input and output of level 0) in scratch buffers: the launches
+    // run on a stream of their own, beside cycles of this grid that the caller
+    // may have in flight.
     // Shapes are timed round-robin (a warm-up round, then NR timed rounds of
     // RL back-to-back launches each, no host wait in between) so that clock
     // and cache drift affect every shape alike; the median round decides.
     constexpr int NR = 5, RL = 3;
     int best = 0;
     const int64_t N0 = hs.lev[0].N;
-    void *in = nullptr, *out = nullptr;
+    const int64_t Nf = l == 0 ? 0 : (hs.lev[l].N + 31) / 32 * 32, Nc = (hs.lev[l + 1].N + 31) / 32 * 32;   // whole 256 bytes
+    const size_t sc = fp32 ? sizeof(float2) : sizeof(double2);
+    void *in = nullptr, *out = nullptr, *fe = nullptr;
     hipStream_t st = nullptr;
     hipEvent_t ev[HH_NTILE][NR][2] = {};
     bool ok = hipStreamCreateWithFlags(&st, hipStreamNonBlocking) == hipSuccess;
@@ -1010,6 +1014,8 @@ static int tune_leg(const hh_grid *g, bool fp32, int leg, int l)
     if (ok && l == 0)
         ok = hipMalloc(&in, sizeof(double2) * N0) == hipSuccess && hipMalloc(&out, sizeof(double2) * N0) == hipSuccess &&
              hipMemsetAsync(in, 0, sizeof(double2) * N0, st) == hipSuccess;
+    if (ok)
+        ok = hipMalloc(&fe, 2 * sc * (Nf + Nc)) == hipSuccess && hipMemsetAsync(fe, 0, 2 * sc * (Nf + Nc), st) == hipSuccess;
     if (ok) {
         Ctx c;
         c.P = g->pd_static_dev;
@@ -1018,9 +1024,23 @@ static int tune_leg(const hh_grid *g, bool fp32, int leg, int l)
         c.L = fp32 ? (const void *)g->L32 : (const void *)g->L64;
         c.omega = hs.omega;
         c.nu1 = hs.nu1;
+        LevelDev<double> l64[HH_MAXLEV];
+        LevelDev<float> l32[HH_MAXLEV];
+        auto scratch = [&](auto *lv, const auto *of, auto *p) {
+            lv[l] = of[l];
+            lv[l + 1] = of[l + 1];
+            if (l > 0) {
+                lv[l].f = p;
+                lv[l].e = p + Nf;
+            }
+            lv[l + 1].f = p + 2 * Nf;
+            lv[l + 1].e = p + 2 * Nf + Nc;
+        };
+        scratch(l64, g->L64h, (double2 *)fe);
+        scratch(l32, g->L32h, (float2 *)fe);
         LvHost lh;
-        lh.d = g->L64h;
-        lh.f = g->L32h;
+        lh.d = l64;
+        lh.f = l32;
         const int ns = tile_shapes(hs.dim);
         int nt[HH_NTILE];
         for (int v = 0; v < ns; ++v) {
@@ -1059,6 +1079,7 @@ static int tune_leg(const hh_grid *g, bool fp32, int leg, int l)
     if (st) (void)hipStreamSynchronize(st);
     if (in) (void)hipFree(in);
     if (out) (void)hipFree(out);
+    if (fe) (void)hipFree(fe);
     for (int v = 0; v < HH_NTILE; ++v)
         for (int r = 0; r < NR; ++r)
             for (int q = 0; q < 2; ++q)
