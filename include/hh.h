@@ -102,6 +102,11 @@ typedef enum { HH_COARSE_REDISCRETISED = 0, HH_COARSE_GALERKIN = 1 } hh_coarse_o
  * it).  Its triangular solves are sequential along anti-diagonals, so a
  * cycle costs about (n_x + n_y) dependent steps per level (rediscretised)
  * or (n_x + 3 n_y) (Galerkin), rows in flight as a pipeline of workgroups.
+ * A workgroup of it only waits for others that run, so a cycle ends whatever
+ * else the device runs.  One cycle at a time may use a grid; where several
+ * overlap on one all the same, a wait can give up after some tens of seconds:
+ * u then holds NaN (hh_vcycle has returned HH_OK; a solve ends with
+ * HH_ERR_NONFINITE).
  * The device copy of the factors is stored in the solves' step order, padded
  * at both ends of each run of 64 (32) rows (1 + 64 / n_x, resp. 1 + 96 / n_x
  * times the entries), with a work array and channel of about as many values

@@ -1822,9 +1822,11 @@ template <bool GAL> struct IluLayout {
     __host__ __device__ int64_t lo(int64_t dd, int k, int t) const { return (dd * S::NLO + k) * TS + t; }
     __host__ __device__ int64_t up(int64_t dd, int k, int t) const { return (DT * S::NLO + dd * (S::NLO + 1) + k) * TS + t; }
     __host__ __device__ int64_t size() const { return DT * (2 * S::NLO + 1) * TS; }
-    // the row form's channel between stages (64-bit words): the launch number,
-    // then per solve, stage and column 4 words for each of the HR rows
-    __host__ __device__ int64_t chan_words() const { return 1 + 2 * (int64_t)nb * nx * S::HR * 4; }
+    // the row form's channel between stages (64-bit words): the launch number
+    // and the stages taken (high and low half); per stage the one that its
+    // workgroup solved before it; then per solve, stage and column 4 words for
+    // each of the HR rows
+    __host__ __device__ int64_t chan_words() const { return 1 + nb + 2 * (int64_t)nb * nx * S::HR * 4; }
 };
 
 // the pointwise phases of the up-leg at point p: u = 0 + P e_{l+1} (bilinear,
@@ -1894,7 +1896,7 @@ __global__ __launch_bounds__(HH_ILU_PW) void k_ilu_skew(Ctx cx, IluArgs a, int t
     const int nx = a.fl.n[0];
     const IluLayout<GAL> lay(nx, a.fl.n[1]);
     const int b = (int)blockIdx.x / tiles, j0 = lay.j0(b), R = lay.j0(b + 1) - j0, nd = nx + S::M * (R - 1), s0 = ((int)blockIdx.x - b * tiles) * SK;
-    if (!UPDATE && blockIdx.x == 0 && threadIdx.x == 0) a.chan[0] = a.chan[0] + 1;   // the solves' launch number
+    if (!UPDATE && blockIdx.x == 0 && threadIdx.x == 0) a.chan[0] = ((a.chan[0] >> 32) + 1) << 32;   // a new launch, no stage taken
     if (s0 >= nd) return;      // uniform
     double2 *w = a.fl.w + (lay.d0(b) + s0) * RW;
     const int nw = min(SK, nd - s0) * RW;
@@ -2003,8 +2005,8 @@ __global__ __launch_bounds__(HH_ILU_WG) void k_ilu_up(Ctx cx, IluArgs a)
 }
 
 // The row form of the triangular solves: the level's rows are cut into stages
-// of at most RW rows (IluLayout's bands), one workgroup per stage, all stages
-// in flight at once as a pipeline.  Within a stage, row r solves point (d - m r,
+// of at most RW rows (IluLayout's bands), a workgroup per stage at a time, the
+// stages in flight as a pipeline.  Within a stage, row r solves point (d - m r,
 // r) on step d; stage b + 1 follows stage b a little more than m RW steps
 // behind, reading the rows it needs (two with m = 3, one with m = 1) from a
 // channel in global memory.  The backward solve is the same walk mirrored
@@ -2029,6 +2031,12 @@ __global__ __launch_bounds__(HH_ILU_WG) void k_ilu_up(Ctx cx, IluArgs a)
 // Channel words carry 32 bits of data and the launch's number (epoch), stored
 // and loaded as relaxed 64-bit atomics at device scope: a word with the
 // current number is the value, so no fence and no clearing is needed.
+// A workgroup takes its stages by a counter, in order, so the stage before one
+// taken was taken by a workgroup that runs; backward it solves the stages it
+// took, last first, so the first of all that remain always has its workgroup at
+// it.  No wait then depends on a workgroup that has not started: the solves end
+// however few workgroups the device runs at a time, beside other streams and
+// processes.
 // Bound: the dependent steps, n_x + about 1.3 m n_y per solve, each about the
 // issue time of one wave's instructions.  One workgroup per level took 0.8-1.2
 // us per step (every row's loads, a barrier and the neighbour reads); as a
@@ -2237,7 +2245,7 @@ __device__ __forceinline__ void ilu_stage(const IluLds &sm, const IluArgs &a, co
         static_assert(NI <= 64, "one channel item per lane");
         const int half = lane & 1, part = lane >> 1 & 1, h = S::HR == 2 ? lane >> 2 & 1 : 0, is = lane / (4 * S::HR);
         const int64_t cw = (int64_t)nx * S::HR * 4;      // words per stage
-        uint64_t *ch = a.chan + 1 + (FWD ? 0 : lay.nb * cw) + (h * 4 + part * 2 + half);
+        uint64_t *ch = a.chan + 1 + lay.nb + (FWD ? 0 : lay.nb * cw) + (h * 4 + part * 2 + half);
         const bool first = FWD ? b == 0 : b == lay.nb - 1;
         // the item's place for chunk c, null where the rows above are not there
         auto item = [&](int c) -> const uint64_t * {
@@ -2260,8 +2268,8 @@ __device__ __forceinline__ void ilu_stage(const IluLds &sm, const IluArgs &a, co
                     v = __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                     ok = (int)((uint32_t)(v >> 32) - epoch) >= 0;
                 }
-                // a stage before that never comes (it cannot, with every
-                // workgroup resident) ends as NaN instead of a hang
+                // a stage before that never comes (it cannot, while one cycle
+                // at a time uses the grid) ends as NaN instead of a hang
                 if (n >= (*sm.failed ? 0 : HH_ILU_SPIN)) {
                     *sm.failed = 1;
                     break;
@@ -2347,15 +2355,29 @@ __global__ __launch_bounds__(HH_ILU_ROWS_WG, 1) void k_ilu_up_rows(Ctx cx, IluAr
     __shared__ double2 rhs[3 * Z::RHS];
     __shared__ double2 ring[Z::RING];
     __shared__ int failed;
+    __shared__ uint64_t taken;
     if (phase_of(cx, 0) != PH_RUN) return;
     const IluLds sm{fac, rhs, ring, &failed};
     const IluLayout<GAL> lay(a.fl.n[0], a.fl.n[1]);
-    const uint32_t epoch = (uint32_t)a.chan[0];
     if (threadIdx.x == 0) failed = 0;
-    const int g = (int)blockIdx.x, G = (int)gridDim.x;
-    int b = g;
-    for (; b < lay.nb; b += G) ilu_stage<GAL, true>(sm, a, lay, b, epoch);
-    for (b -= G; b >= 0; b -= G) ilu_stage<GAL, false>(sm, a, lay, b, epoch);
+    uint64_t *before = a.chan + 1;      // the stage its workgroup solved before each stage
+    int last = -1;
+    uint32_t epoch = 0;
+    for (;;) {
+        if (threadIdx.x == 0) taken = __hip_atomic_fetch_add(a.chan, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        __syncthreads();
+        const int b = __builtin_amdgcn_readfirstlane((int)(uint32_t)taken);
+        epoch = __builtin_amdgcn_readfirstlane((uint32_t)(taken >> 32));
+        if (b >= lay.nb) break;
+        if (threadIdx.x == 0) __hip_atomic_store(before + b, (uint64_t)(int64_t)last, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        ilu_stage<GAL, true>(sm, a, lay, b, epoch);     // ends with a barrier
+        last = b;
+    }
+    while (last >= 0) {
+        const int next = (int)__hip_atomic_load(before + last, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        ilu_stage<GAL, false>(sm, a, lay, last, epoch);
+        last = __builtin_amdgcn_readfirstlane(next);
+    }
 }
 
 // ---------------------------------------------------------------------------

@@ -1256,13 +1256,15 @@ template <typename T> static TailArgs<T> tail_args(const Plan &pl)
 
 // Workgroups of the row form: a stage runs for about nx + m RW steps and the
 // next one starts m RW steps or more behind it, so at most 2 + nx / (m RW) are
-// ever in flight; a workgroup takes stages g, g + G, ... in order.  All of them
-// must be resident at once (they wait for each other): at most 32, one per CU
-// (LDS), leaves room for as many launches as the device has queues.
+// ever in flight; one whose stage is done takes the next.  At most 32, one per
+// CU (LDS): more would leave other streams' launches fewer CUs.  The solves end
+// with any number of them running (k_ilu_up_rows); HH_ILU_GROUPS sets another.
 template <bool GAL> static int ilu_groups(int nx, int ny)
 {
     using S = IluSet<GAL>;
-    return std::min(std::min(IluLayout<GAL>(nx, ny).nb, 2 + nx / (S::M * S::RW)), 32);
+    const int nb = IluLayout<GAL>(nx, ny).nb;
+    if (const char *e = getenv("HH_ILU_GROUPS")) return std::min(nb, std::max(1, atoi(e)));
+    return std::min(std::min(nb, 2 + nx / (S::M * S::RW)), 32);
 }
 
 // residual, solves and update of one level in the row form
@@ -1328,7 +1330,7 @@ static void vcycle_t(const Plan &pl, int fsel, int osel, const void *fptr, void 
     if (pl.mK) launch_merged<T>(1, pl, s, lh, fptr, optr);
     if constexpr (DIM == 2 && std::is_same<T, double>::value) {
         if (pl.ilu) {
-            // ILU(0) up-legs (one problem): one workgroup per level
+            // ILU(0) up-legs (one problem)
             const Ctx c = ctx_of(pl, pl.chunks);
             for (int l = pl.Lmax - 1; l >= 0; --l) {
                 IluArgs a;
