@@ -155,11 +155,11 @@ __device__ __forceinline__ void idr_finalize(const ProbDev *pd, int kind, bool g
                 oldest = oldest + 1 == s ? 0 : oldest + 1;
                 kstep = kstep + 1 == s + 1 ? 0 : kstep + 1;
             }
-            __builtin_amdgcn_wave_barrier();
+            wave_order();           // G and m, a row per lane, to the lanes of the solve
             if (!small_solve(st.G, s, st.m, st.c)) halt(RS_BREAK);
         };
         step();
-        __builtin_amdgcn_wave_barrier();
+        wave_order();               // c, a row per lane, to the lane that mirrors it
         if (t == 0) {
             st.phase = phase;
             st.reason = reason;

@@ -68,6 +68,18 @@ __device__ inline double lane_value(double v, int l)
     return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(v), l), __builtin_amdgcn_readlane(__double2loint(v), l));
 }
 
+// Order between lanes of one wave that exchange values through memory: what any
+// lane wrote before is there for any lane that reads after.  LDS serves a
+// wave's accesses in order, so it takes no instruction; without it the compiler
+// may move a read over another lane's write, since the addresses that one
+// thread uses do not meet.
+__device__ __forceinline__ void wave_order()
+{
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
 // Pairwise tree over the 64 lanes of a wave (all lanes active); every lane
 // gets the sum.  Aligned blocks of 1, 2, 4 and 8 lanes are paired with the
 // neighbouring block by DPP (xor 1 and xor 2 by quad permutes, then the
@@ -2218,6 +2230,7 @@ __device__ __forceinline__ void ilu_stage(const IluLds &sm, const IluArgs &a, co
                 __builtin_amdgcn_sched_barrier(0);
                 ilu_step<FWD>(q[s & 1], w1, s, i0 + s, nxr, part, W1, W2, O);
                 cur[s * ST + (row + S::HR) * S::XE + part] = O[GAL ? s & 1 : 0];
+                wave_order();       // the next step reads other lanes' values
                 __builtin_amdgcn_sched_barrier(0);
             }
             b0 = b1;
