@@ -657,7 +657,7 @@ __global__ __launch_bounds__(HH_FIN_WG) void k_fin1(int kind, ProbDev pv, int re
     finalize(&pv, kind, true, red ? 1 : pv.ngroup);
 }
 
-// Many partials: one workgroup per value and problem (blockIdx.x, .y) leaves
+// Many partials: one workgroup per problem and value (blockIdx.x, .y) leaves
 // the value's sum in place of its first partial, so that the finaliser's one
 // CU has as many values to read as the pass has.  One CU takes 9 us for the 9
 // x 4096 partials of IDR(4) at 128^3; these workgroups and their launch take
@@ -666,9 +666,9 @@ __global__ __launch_bounds__(HH_FIN_WG) void k_fin1(int kind, ProbDev pv, int re
 #define HH_RED_WG 256
 __global__ __launch_bounds__(HH_RED_WG) void k_red(Ctx cx, const int *__restrict__ probs, int kind)
 {
-    const int prob = probs ? probs[blockIdx.y] : 0;
+    const int prob = probs ? probs[blockIdx.x] : 0;
     const ProbDev *pd = cx.P + prob;
-    const int v = (int)blockIdx.x;
+    const int v = (int)blockIdx.y;
     const HH_GLOBAL int *ct = cx.ctrl ? (const HH_GLOBAL int *)(cx.ctrl + prob) : nullptr;
     if (ct && !fin_runs(kind, ct[0])) return;
     int value = v;

@@ -1392,7 +1392,8 @@ void launch_fin(const Plan &pl, const int *probs, int n, int kind, hipStream_t s
     const int nv = step ? 1 + 2 * ns : kind == FIN_IDR_OMEGA ? 3 : fin_values(kind);
     const int red = kind != FIN_IDR_INIT && (int64_t)nv * ng >= HH_RED_MIN ? 1 : 0;
     const int *pr = pl.count == 1 ? nullptr : probs;
-    if (red) hipLaunchKernelGGL(k_red, dim3(step ? 1 + 2 * HH_MAX_S + 2 * ns : nv, n), dim3(HH_RED_WG), 0, s, c, pr, kind);
+    // (problems in x: any number of them; y takes 65,535)
+    if (red) hipLaunchKernelGGL(k_red, dim3(n, step ? 1 + 2 * HH_MAX_S + 2 * ns : nv), dim3(HH_RED_WG), 0, s, c, pr, kind);
     if (pl.count == 1 && !pl.host.empty())
         hipLaunchKernelGGL(k_fin1, dim3(1), dim3(HH_FIN_WG), 0, s, kind, pl.host[0], red);
     else
