@@ -80,7 +80,7 @@ __device__ __forceinline__ bool small_solve(const double2 *G, int s, const doubl
 // of G and m in lane i) and copied back: a chain of dependent global accesses
 // by one thread cost more than the sums.  Passes that reduce nothing in the
 // current mode (omega in steps k >= 1) return after the copy.
-__device__ __forceinline__ void idr_finalize(const ProbDev *pd, int kind, bool gate, int ng)
+__device__ __forceinline__ void idr_finalize(const ProbDev *pd, int kind, int ng)
 {
     constexpr int SW = sizeof(SolveState) / 4, CW = sizeof(Ctrl) / 4;
     static_assert(sizeof(SolveState) % 4 == 0 && sizeof(Ctrl) % 4 == 0 && SW <= HH_FIN_WG && CW <= HH_FIN_WG, "one word per thread");

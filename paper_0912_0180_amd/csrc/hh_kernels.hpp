@@ -407,7 +407,7 @@ __device__ inline void mirror(Ctrl &c, const SolveState &st)
 }
 
 // defined with the IDR kernels
-__device__ __forceinline__ void idr_finalize(const ProbDev *pd, int kind, bool gate, int ng);
+__device__ __forceinline__ void idr_finalize(const ProbDev *pd, int kind, int ng);
 
 // Scalar state of a Bi-CGSTAB solve, copied to registers before the
 // reduction (its loads overlap the partial sums) and written back once.
@@ -462,7 +462,7 @@ __host__ __device__ inline int fin_values(int kind)
 __device__ __forceinline__ void finalize(const ProbDev *pd, int kind, bool gate, int ng)
 {
     if (kind >= FIN_IDR_OMEGA) {
-        idr_finalize(pd, kind, gate, ng);
+        idr_finalize(pd, kind, ng);
         return;
     }
     SolveState *st = pd->st;
@@ -2173,7 +2173,7 @@ __device__ __forceinline__ void ilu_step(const IluStep<false, FWD> &q, double2, 
 }
 
 // LDS of the row form, arrays of their own (so that the factor reads need not
-// wait for the ring writes): two chunk buffers of factors and of right-hand
+// wait for the ring writes): three chunk buffers of factors and of right-hand
 // sides, and the ring of solved values, rows -HR .. RW - 1 per step
 template <bool GAL> struct IluLdsSize {
     using S = IluSet<GAL>;
