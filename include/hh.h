@@ -107,10 +107,12 @@ typedef enum { HH_COARSE_REDISCRETISED = 0, HH_COARSE_GALERKIN = 1 } hh_coarse_o
  * overlap on one all the same, a wait can give up after some tens of seconds:
  * u then holds NaN (hh_vcycle has returned HH_OK; a solve ends with
  * HH_ERR_NONFINITE).
- * The device copy of the factors is stored in the solves' step order, padded
- * at both ends of each run of 64 (32) rows (1 + 64 / n_x, resp. 1 + 96 / n_x
- * times the entries), with a work array and channel of about as many values
- * as points. */
+ * The device copy of the factors is stored in the solves' step order, by runs
+ * of at most 64 (rediscretised) or 32 (Galerkin) rows, each padded to the full
+ * number and at both ends: at most r / n_y + 64 / n_x, resp. r / n_y + 96 / n_x
+ * times the entries, r = n_y rounded up to whole runs.  A work array takes as
+ * many times the points, and a channel 4 (8) n_x values per run.
+ * hh_grid_query gives the bytes a grid holds. */
 typedef enum { HH_SMOOTH_JACOBI = 0, HH_SMOOTH_ILU0 = 1 } hh_smoother;
 
 /* Grid description (host memory, read during hh_setup_grid only). */
