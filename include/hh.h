@@ -222,9 +222,9 @@ hh_status hh_vcycle(const hh_grid *g, hh_prec prec, const void *f, void *u, void
  * down-leg and up-leg of the finest level, launched exactly as hh_vcycle and
  * the solves launch them.  Times are averages, from HIP events on `stream`,
  * over `reps` back-to-back cycles and then `reps` back-to-back launches of
- * each leg.  2D grids of at most 65,536 unknowns run the finest leg and the
- * next levels' as one merged launch, where the sides halve exactly: the leg's
- * time, shape (-1) and workgroups are then that launch's.  f, u as for
+ * each leg.  Small 2D grids (at most 65,536 unknowns) run the finest leg and
+ * the next levels' as one merged launch where that is faster: the leg's time,
+ * shape (-1) and workgroups are then that launch's.  f, u as for
  * hh_vcycle; u holds V(f) afterwards.  Builds the V-cycle plan like hh_vcycle;
  * creates and destroys six events; synchronises the stream.  Errors: as
  * hh_vcycle, and HH_ERR_ARG for reps < 1 or a null out. */

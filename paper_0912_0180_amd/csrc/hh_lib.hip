@@ -400,7 +400,13 @@ template <> struct MergeTile<double> { static constexpr int C = 2, BC = 2, UT = 
 // latency too: 128^2 FP64 cycle 32 -> 18 us with the next rule), and where
 // k_coarse solves the coarsest level the merged legs end there: the tail
 // kernel's two launches beside it cost more than two more merged levels.
+// In FP64 a down-leg workgroup over three levels from level 0 takes a CU (LDS):
+// with more tiles than the card's 256 CUs they run in two rounds, and level 0
+// stays tiled (320 x 200, 260 tiles: 25.7 us against 30.4 merged; 256^2, 256
+// tiles: 26.5 against 21.8).  In FP32, or over two levels, a CU takes several
+// (320 x 200 FP32: 24.3 against 21.1).
 #define HH_MERGE_TOP 65536
+#define HH_MERGE_CUS 256
 static bool merges(const hh_grid *const *G, int count)
 {
     if (const char *e = getenv("HH_MERGE"))
@@ -418,17 +424,19 @@ static void plan_merge(Plan &pl, const hh_grid *const *G, int count, bool fp32)
     pl.mK = pl.mlev0 = pl.mdn = pl.mKup = pl.mlev0u = pl.mup = 0;
     if (!merges(G, count)) return;
     const HostSetup &hs = G[0]->hs;
-    const int t = plan_tail(G[0], count, fp32), most = hs.lev[0].N <= HH_MERGE_TOP ? t : t - 1;
+    const int t = plan_tail(G[0], count, fp32), C = fp32 ? MergeTile<float>::C : MergeTile<double>::C;
+    const int tiles = ceil_div(hs.lev[t].n[0], C) * ceil_div(hs.lev[t].n[1], C);
+    const bool top = hs.lev[0].N <= HH_MERGE_TOP && (fp32 || t != 3 || tiles <= HH_MERGE_CUS);
+    const int most = top ? t : t - 1;
     const int K = std::min(3, most), Kup = std::min(4, most);
     if (K < 2) return;
     for (int l = t - Kup; l < t; ++l)
         if (hs.lev[l].n[0] != 2 * hs.lev[l + 1].n[0] || hs.lev[l].n[1] != 2 * hs.lev[l + 1].n[1]) return;
-    const int C = fp32 ? MergeTile<float>::C : MergeTile<double>::C;
     const int UT = Kup == 4 ? (fp32 ? MergeTile<float>::UT4 : MergeTile<double>::UT4)
                             : (fp32 ? MergeTile<float>::UT : MergeTile<double>::UT);
     pl.mK = K;
     pl.mlev0 = t - K;
-    pl.mdn = ceil_div(hs.lev[t].n[0], C) * ceil_div(hs.lev[t].n[1], C);
+    pl.mdn = tiles;
     pl.mKup = Kup;
     pl.mlev0u = t - Kup;
     pl.mup = ceil_div(hs.lev[t - Kup].n[0], UT) * ceil_div(hs.lev[t - Kup].n[1], UT);
