@@ -15,7 +15,7 @@ ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libhh.so")
 SOURCES = ["hh_setup.cpp", "hh_lib.hip", "hh_solve.hip", "hh_select.hip", "hh_server.cpp"]
-HEADERS = ["hh_common.h", "hh_kernels.hpp", "hh_lib.h", "hh_setup.h", "hh_idr_kernels.hpp"]
+HEADERS = ["hh_common.h", "hh_kernels.hpp", "hh_lib.h", "hh_merge.h", "hh_setup.h", "hh_idr_kernels.hpp"]
 ARCH = os.environ.get("HH_OFFLOAD_ARCH", "gfx950")
 
 FLAGS = ["-O3", "-std=c++17", "-fPIC", "-ffp-contract=off", "-Wall", "-Wno-unused-function",

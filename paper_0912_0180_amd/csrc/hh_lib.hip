@@ -18,6 +18,7 @@
 #include "hh_kernels.hpp"
 #include "hh_idr_kernels.hpp"
 #include "hh_lib.h"
+#include "hh_merge.h"
 #include "hh_setup.h"
 
 using namespace hh;
@@ -382,10 +383,10 @@ static void grid_release(hh_grid *g)
 }
 
 // ---------------------------------------------------------------------------
-// Merged coarse legs (one 2D problem; batches: batch_merge), each level exactly twice the next: the
-// down-legs of the last K = 2 or 3 levels above the tail run as one launch,
+// Merged coarse legs (one 2D problem; batches: batch_merge), each level exactly
+// twice the next: the down-legs of the last K = 2 or 3 levels run as one launch,
 // the up-legs of the last 2 to 4 (their regions stay small) as another.
-// Down: C x C tiles of the tail's first level.  Up: UT x UT tiles of the
+// Down: C x C tiles of the level below them.  Up: UT x UT tiles of the
 // first merged up level, UT = 16 over up to three levels and 32 over four
 // (about 256 workgroups either way: more would not all be resident at once).
 // NT threads (four waves per SIMD hide the LDS latency of the per-point
@@ -461,13 +462,23 @@ static void plan_merge(Plan &pl, const hh_grid *const *G, int count, bool fp32)
 //   32 of 256 .. 768          805  1166 -> 1231  1115 -> 1216
 //   8 of 128 .. 512, coarsest 8^2 .. 11^2: the tail kernel solves them all
 //                                   294 ->  294   195 ->  195
-// A workgroup takes a CU (LDS), so more tiles than CUs run one after another,
-// each with its halo's extra work; and a batch whose tail kernel solves every
-// coarsest grid (none over HH_SPLIT_NC) has one launch there already.
+// So not above HH_BMERGE_AREA tiles (the FP32 legs' workgroups on 256 CUs; the
+// FP64 legs have up to 2.25 times as many), not where no coarsest grid is over
+// HH_SPLIT_NC (the tail kernel is one launch there already), and below that
+// where the launches saved are worth the workgroups' rounds in the precision
+// at hand (batch_merge_pays).
 // The down-legs take tiles of BC coarsest points: 12.4 us with 2, 8.0 with 3,
 // 9.2 with 4 for 8 of 256 .. 768 in FP32; 2 in FP64, where 3 would not fit LDS.
 #define HH_BMERGE_AREA 256
-static std::vector<int> batch_merge(const std::vector<const hh_grid *> &G)
+// workgroups of problem hs in a batch's merged legs
+static void batch_groups(const HostSetup &hs, bool fp32, int &nd, int &nu)
+{
+    const int c = hs.nlev - 1, kup = batch_kup(hs.nlev), UT = batch_ut(kup);
+    const int C = fp32 ? MergeTile<float>::BC : MergeTile<double>::BC;
+    nd = ceil_div(hs.lev[c].n[0], C) * ceil_div(hs.lev[c].n[1], C);
+    nu = ceil_div(hs.lev[c - kup].n[0], UT) * ceil_div(hs.lev[c - kup].n[1], UT);
+}
+static std::vector<int> batch_merge(const std::vector<const hh_grid *> &G, bool fp32)
 {
     std::vector<int> on(G.size(), 0);
     if (G.size() < 2) return on;
@@ -475,19 +486,32 @@ static std::vector<int> batch_merge(const std::vector<const hh_grid *> &G)
         if (atoi(e) == 0) return on;
     int64_t area = 0;
     bool any = false;   // some problem has its coarsest grid solved by k_coarse anyhow
+    std::vector<BatchShape> shapes;
     for (size_t q = 0; q < G.size(); ++q) {
         const HostSetup &hs = G[q]->hs;
         const int c = hs.nlev - 1;
-        if (hs.dim != 2 || G[q]->host_only || batch_kdown(hs.nlev) < 2) continue;
-        bool exact = true;
-        for (int l = c - batch_kup(hs.nlev); l < c; ++l)
-            exact = exact && hs.lev[l].n[0] == 2 * hs.lev[l + 1].n[0] && hs.lev[l].n[1] == 2 * hs.lev[l + 1].n[1];
-        if (!exact) continue;
-        on[q] = 1;
-        any = any || coarse_split(hs);
-        area += (int64_t)ceil_div(hs.lev[c].n[0], 3) * ceil_div(hs.lev[c].n[1], 3);
+        if (hs.dim != 2 || G[q]->host_only) return std::vector<int>(G.size(), 0);
+        BatchShape s{};
+        s.levels = hs.nlev;
+        s.tail = tail_level(hs, fp32);
+        s.split = coarse_split(hs);
+        bool exact = batch_kdown(hs.nlev) >= 2;
+        for (int l = c - batch_kup(hs.nlev); exact && l < c; ++l)
+            exact = hs.lev[l].n[0] == 2 * hs.lev[l + 1].n[0] && hs.lev[l].n[1] == 2 * hs.lev[l + 1].n[1];
+        if (exact) {
+            int nd, nu;
+            batch_groups(hs, fp32, nd, nu);
+            on[q] = s.on = 1;
+            s.kdown = batch_kdown(hs.nlev);
+            s.kup = batch_kup(hs.nlev);
+            s.down = nd;
+            s.up = nu;
+            any = any || s.split;
+            area += (int64_t)ceil_div(hs.lev[c].n[0], 3) * ceil_div(hs.lev[c].n[1], 3);
+        }
+        shapes.push_back(s);
     }
-    if (!any || area > HH_BMERGE_AREA) on.assign(G.size(), 0);
+    if (!any || area > HH_BMERGE_AREA || !batch_merge_pays(shapes.data(), (int)shapes.size(), fp32)) on.assign(G.size(), 0);
     return on;
 }
 
@@ -706,7 +730,7 @@ hh_status plan_build(Plan &pl, const std::vector<const hh_grid *> &G, bool fp32)
     std::vector<int> fin, tail;
     pl.tail_down = pl.tail_up = false;
     plan_merge(pl, G.data(), (int)G.size(), fp32);
-    const std::vector<int> bm = batch_merge(G);
+    const std::vector<int> bm = batch_merge(G, fp32);
     // levels of problem q with tiled down- and up-legs
     auto ntiled = [&](int q, int leg) {
         const int c = G[q]->hs.nlev - 1;
@@ -735,11 +759,8 @@ hh_status plan_build(Plan &pl, const std::vector<const hh_grid *> &G, bool fp32)
             for (int i = 0; i < nwg; ++i) coarse.push_back(Tile{q, i});
         }
         if (bm[q]) {
-            const int Kup = batch_kup(hs.nlev), UT = batch_ut(Kup);
-            const HostLevel &Lu = hs.lev[c - Kup];
-            const int C = fp32 ? MergeTile<float>::BC : MergeTile<double>::BC;
-            const int nd = ceil_div(hs.lev[c].n[0], C) * ceil_div(hs.lev[c].n[1], C);
-            const int nu = ceil_div(Lu.n[0], UT) * ceil_div(Lu.n[1], UT);
+            int nd, nu;
+            batch_groups(hs, fp32, nd, nu);
             for (int i = 0; i < nd; ++i) bdn.push_back(Tile{q, i});
             for (int i = 0; i < nu; ++i) bup.push_back(Tile{q, i});
         } else {
