@@ -3911,9 +3911,9 @@ template <typename T> __host__ __device__ inline int coarse_waves(int n)
 // Coarsest solve e = Minv f with the rows spread over workgroups: wave w of
 // the problem takes rows w, w + W, ... (W waves in all), each row summed
 // exactly as in the tail kernel.  f is staged in LDS.  SEG = coarse_seg(Nc) of
-// a single problem; 0: one launch for all problems of a batch, whatever theirs
-// (a uniform branch; 4.8 us where two launches took 9.6, but the code of all
-// five forms costs a single cycle about 0.5 us).
+// every problem in the launch; 0: of each its own (a uniform branch; 4.8 us
+// where two launches took 9.6, but the code of all five forms costs a cycle
+// about 0.5 us).
 template <typename T, int SEG>
 __global__ __launch_bounds__(HH_WG) void k_coarse(Ctx cx)
 {

@@ -22,6 +22,7 @@ struct Plan {
     bool fp32 = false;
     DevList chunks, down[HH_MAXLEV], up[HH_MAXLEV];   // down/up: levels above the tail
     DevList coarse;                  // k_coarse workgroups
+    int cseg = 0;                    // segment length of all their coarsest grids, 0: several (see k_coarse)
     bool tail_down = false;          // some problem needs the (full or down-only) tail kernel
     bool tail_up = false;            // some problem needs the up-only tail kernel
     int vdv[HH_MAXLEV] = {}, vuv[HH_MAXLEV] = {};   // tile shape of each level's down- and up-leg

@@ -755,6 +755,7 @@ hh_status plan_build(Plan &pl, const std::vector<const hh_grid *> &G, bool fp32)
         const bool split = coarse_split(hs);
         pl.Lmax = std::max(pl.Lmax, std::max(ntiled(q, 0), ntiled(q, 1)));
         if (split || bm[q]) {
+            pl.cseg = coarse.empty() || pl.cseg == coarse_seg(hs.Nc) ? coarse_seg(hs.Nc) : 0;
             const int nwg = ceil_div(fp32 ? coarse_waves<float>(hs.Nc) : coarse_waves<double>(hs.Nc), HH_WG / 64);
             for (int i = 0; i < nwg; ++i) coarse.push_back(Tile{q, i});
         }
@@ -1165,6 +1166,7 @@ static void plan_host_one(Plan &pl, const hh_grid *g, bool fp32, const void *L1,
     }
     pl.coarse.n = 0;
     const bool split = coarse_split(hs);
+    pl.cseg = coarse_seg(hs.Nc);
     if (split) {
         pl.coarse.n = ceil_div(fp32 ? coarse_waves<float>(hs.Nc) : coarse_waves<double>(hs.Nc), HH_WG / 64);
     }
@@ -1340,7 +1342,7 @@ static void vcycle_t(const Plan &pl, int fsel, int osel, const void *fptr, void 
             else
                 hipLaunchKernelGGL((k_vtail<DIM, T, false>), dim3(pl.ntail), dim3(TailCap<T>::WG), 0, s, c, probs, 0, TailArgs<T>{});
         }
-        switch (pl.count == 1 ? coarse_seg(pl.pd1.Nc) : 0) {
+        switch (pl.cseg) {
         case 0: LAUNCH((k_coarse<T, 0>), pl.coarse.n, s, ctx_of(pl, pl.coarse)); break;
         case 1: LAUNCH((k_coarse<T, 1>), pl.coarse.n, s, ctx_of(pl, pl.coarse)); break;
         case 2: LAUNCH((k_coarse<T, 2>), pl.coarse.n, s, ctx_of(pl, pl.coarse)); break;
