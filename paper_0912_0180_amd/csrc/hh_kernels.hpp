@@ -351,7 +351,11 @@ __device__ __forceinline__ void reduce_partials(const double *part, int stride, 
             double v[B][L];
 #pragma unroll
             for (int b = 0; b < B; ++b) {
-                const int g = min(g0 + b * nw, T - 1), q = value_of(g), e0 = (g - q * U) * HH_FIN_UNIT + L * lane;
+                // (units past the last are not loaded: loads clamped to it cost
+                // small solves 2 to 4%, 8^3 Bi-CGSTAB 3.69 -> 3.55 ms per 96 matvecs)
+                const int g = g0 + b * nw;
+                if (g >= T) break;     // uniform over the wave
+                const int q = value_of(g), e0 = (g - q * U) * HH_FIN_UNIT + L * lane;
                 const double *p = part + (int64_t)(first + q0 + q) * stride;
                 if (e0 + L <= n) {
 #pragma unroll
