@@ -2053,12 +2053,14 @@ __global__ __launch_bounds__(HH_ILU_WG) void k_ilu_up(Ctx cx, IluArgs a)
 // it.  No wait then depends on a workgroup that has not started: the solves end
 // however few workgroups the device runs at a time, beside other streams and
 // processes.
-// Bound: the dependent steps, n_x + about 1.3 m n_y per solve, each about the
-// issue time of one wave's instructions.  One workgroup per level took 0.8-1.2
-// us per step (every row's loads, a barrier and the neighbour reads); as a
-// pipeline a 25-point step takes about 500 cycles forward and 600 backward (a
-// complex division), a 5-point one 220 and 400: 0.26 and 0.18 us on average,
-// the stages' lag included.
+// Bound: the dependent steps, n_x + about 1.3 m n_y per solve, one wave's chain.
+// One workgroup per level took 0.8-1.2 us per step (every row's loads, a
+// barrier and the neighbour reads); as a pipeline a 25-point step takes about
+// 500 cycles forward and 600 backward (a complex division), a 5-point one 220
+// and 400: 0.26 and 0.18 us on average, the stages' lag included.  About half
+// is issue: 55 and 74 vector instructions a step (5-point 27 and 58), 4 cycles
+// each; the rest is latency: up to 16 LDS reads a step, the newest neighbour's
+// value through the ring among them, and dependent FP64 operations.
 // ILU(0) V-cycle with the residual and update through LDS tiles (k_ilu_skew),
 // 384^2: 3.48 -> 1.09 ms; 1280^2: 17.0 -> 3.95 ms.
 // Values and operation order are k_ilu_up's: a product f q is taken as
