@@ -2062,7 +2062,7 @@ __global__ __launch_bounds__(HH_ILU_WG) void k_ilu_up(Ctx cx, IluArgs a)
 // each; the rest is latency: up to 16 LDS reads a step, the newest neighbour's
 // value through the ring among them, and dependent FP64 operations.
 // ILU(0) V-cycle with the residual and update through LDS tiles (k_ilu_skew),
-// 384^2: 3.48 -> 1.09 ms; 1280^2: 17.0 -> 3.95 ms.
+// 384^2: 3.48 -> 1.08 ms; 1280^2: 17.0 -> 3.92 ms.
 // Values and operation order are k_ilu_up's: a product f q is taken as
 // (f.x a + f.y b) with (a, b) = (q.x, -q.y) resp. (q.y, q.x), which rounds as
 // cmul does; values outside the grid are +0 and their factors +0.
